@@ -305,6 +305,28 @@ int mixfp4_gemm_ws(const uint8_t *a_codes, const uint8_t *a_scales,
                    int64_t workspace_bytes, void *stream);
 
 /*
+ * mixfp4_gemm_auto - mixfp4_gemm with caller-supplied device workspace, on
+ * the route expected to be the fastest for the shape: without workspace
+ * (decode shapes, K % 32 != 0 and small products of K % 64 != 0), with A
+ * decoded once into the workspace and W decoded on its way into the matrix
+ * instructions (m > 16 up to about a thousand rows, K % 64 == 0, K >= 256), or
+ * the two passes of mixfp4_gemm_ws.  The routes differ only in the order of
+ * the fp32 sums.  With workspace == NULL, or less of it than
+ * mixfp4_gemm_auto_workspace_size reports, the call computes what
+ * mixfp4_gemm computes.  Arguments, alignment and errors as for
+ * mixfp4_gemm_ws.
+ *
+ * mixfp4_gemm_auto_workspace_size - bytes of workspace that route needs (0:
+ * none).  Host-only; errors as for mixfp4_gemm_workspace_size.
+ */
+int mixfp4_gemm_auto(const uint8_t *a_codes, const uint8_t *a_scales,
+                     const float *a_tensor_scale, const uint8_t *w_codes,
+                     const uint8_t *w_scales, const float *w_tensor_scale,
+                     int64_t m, int64_t n, int64_t k, float *c, void *workspace,
+                     int64_t workspace_bytes, void *stream);
+int mixfp4_gemm_auto_workspace_size(int64_t m, int64_t n, int64_t k, int64_t *bytes);
+
+/*
  * mixfp4_gemm_noalloc - mixfp4_gemm_ws for callers that cannot allocate
  * device memory (code under HIP graph capture, tight serving loops, hosts
  * that forbid allocation): the workspace is the library's own static device

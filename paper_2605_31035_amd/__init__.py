@@ -336,8 +336,8 @@ def mixfp4_gemm(a, w, out: torch.Tensor | None = None, workspace=None) -> torch.
     (s32 may be None for 1.0).  Returns fp32 [m, n].  ``workspace``: None
     (mixfp4_gemm), a contiguous uint8 CUDA tensor (mixfp4_gemm_ws with it),
     True (mixfp4_gemm_ws with a workspace of mixfp4_gemm_workspace_size bytes
-    allocated here), or "auto" (as True where gemm_two_pass_preferred, else
-    as None)."""
+    allocated here), or "auto" (mixfp4_gemm_auto: the route expected to be
+    the fastest, with the workspace it needs allocated here)."""
     ac, asc, ats = a
     wc, wsc, wts = w
     for name, t in (("A codes", ac), ("W codes", wc)):
@@ -358,11 +358,16 @@ def mixfp4_gemm(a, w, out: torch.Tensor | None = None, workspace=None) -> torch.
     if out is None:
         out = torch.empty((m, n), dtype=torch.float32, device=ac.device)
     _require(out, "out", torch.float32, (m, n))
+    auto = False
     if isinstance(workspace, str):
         if workspace != "auto":
             raise ValueError('workspace must be None, True, "auto" or a uint8 tensor')
-        workspace = True if gemm_two_pass_preferred(m, n, k) else None
-    if workspace is True:
+        auto = True
+        need = ctypes.c_int64(0)
+        _check(lib.mixfp4_gemm_auto_workspace_size(m, n, k, ctypes.byref(need)))
+        workspace = torch.empty(need.value, dtype=torch.uint8, device=ac.device) \
+            if need.value else None
+    elif workspace is True:
         workspace = torch.empty(max(1, mixfp4_gemm_workspace_size(m, n, k)), dtype=torch.uint8,
                                 device=ac.device)
     if workspace is not None:
@@ -376,9 +381,9 @@ def mixfp4_gemm(a, w, out: torch.Tensor | None = None, workspace=None) -> torch.
         st = lib.mixfp4_gemm(_ptr(ac), _ptr(asc), _ptr(ats), _ptr(wc), _ptr(wsc), _ptr(wts),
                              m, n, k, _ptr(out), _stream(ac.device))
     else:
-        st = lib.mixfp4_gemm_ws(_ptr(ac), _ptr(asc), _ptr(ats), _ptr(wc), _ptr(wsc), _ptr(wts),
-                                m, n, k, _ptr(out), _ptr(workspace), workspace.numel(),
-                                _stream(ac.device))
+        call = lib.mixfp4_gemm_auto if auto else lib.mixfp4_gemm_ws
+        st = call(_ptr(ac), _ptr(asc), _ptr(ats), _ptr(wc), _ptr(wsc), _ptr(wts), m, n, k,
+                  _ptr(out), _ptr(workspace), workspace.numel(), _stream(ac.device))
     _check(st)
     return out
 

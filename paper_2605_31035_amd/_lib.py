@@ -16,6 +16,7 @@ LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmixfp4.s
 SYMBOLS = ("mixfp4_quantize", "mixfp4_quantize_ex", "mixfp4_quantize_2d", "mixfp4_hadamard",
            "mixfp4_dequantize",
            "mixfp4_gemm", "mixfp4_gemm_ws", "mixfp4_gemm_workspace_size",
+           "mixfp4_gemm_auto", "mixfp4_gemm_auto_workspace_size",
            "mixfp4_decode_operand", "mixfp4_gemm_decoded", "mixfp4_gemm_noalloc",
            "mixfp4_gemm_noalloc_max_bytes", "mixfp4_decode_step",
            "mixfp4_quantize_variant", "mixfp4_dequantize_variant", "mixfp4_quantize_decode",
@@ -48,6 +49,10 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     h.mixfp4_gemm.restype = i32
     h.mixfp4_gemm_ws.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, vp, vp, i64, vp]
     h.mixfp4_gemm_ws.restype = i32
+    h.mixfp4_gemm_auto.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, vp, vp, i64, vp]
+    h.mixfp4_gemm_auto.restype = i32
+    h.mixfp4_gemm_auto_workspace_size.argtypes = [i64, i64, i64, ctypes.POINTER(i64)]
+    h.mixfp4_gemm_auto_workspace_size.restype = i32
     h.mixfp4_gemm_workspace_size.argtypes = [i64, i64, i64, ctypes.POINTER(i64)]
     h.mixfp4_gemm_workspace_size.restype = i32
     h.mixfp4_decode_operand.argtypes = [vp, vp, i64, i64, vp, i64, ctypes.POINTER(i64), vp]

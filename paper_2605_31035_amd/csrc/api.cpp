@@ -321,6 +321,45 @@ int mixfp4_gemm_ws(const uint8_t* a_codes, const uint8_t* a_scales, const float*
                                            w_tensor_scale, m, n, k, c, s));
 }
 
+int mixfp4_gemm_auto_workspace_size(int64_t m, int64_t n, int64_t k, int64_t* bytes) {
+  if (!bytes) return MIXFP4_ERR_NULL;
+  if (m < 0 || n < 0 || k < 0 || (k % mixfp4::kBlock) != 0) return MIXFP4_ERR_SHAPE;
+  *bytes = mixfp4::gemm_plan(m, n, k).workspace;
+  return MIXFP4_OK;
+}
+
+int mixfp4_gemm_auto(const uint8_t* a_codes, const uint8_t* a_scales, const float* a_tensor_scale,
+                     const uint8_t* w_codes, const uint8_t* w_scales, const float* w_tensor_scale,
+                     int64_t m, int64_t n, int64_t k, float* c, void* workspace,
+                     int64_t workspace_bytes, void* stream) {
+  const int st = gemm_check(a_codes, a_scales, a_tensor_scale, w_codes, w_scales, w_tensor_scale,
+                            m, n, k, c);
+  if (st != MIXFP4_OK) return st == kEmpty ? MIXFP4_OK : st;
+  if (workspace_bytes < 0) return MIXFP4_ERR_SHAPE;
+  if (workspace && !aligned(workspace, 256)) return MIXFP4_ERR_ALIGN;
+  (void)hipGetLastError();
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const mixfp4::GemmPlan plan = mixfp4::gemm_plan(m, n, k);
+  // a W whose scale bytes are not word aligned is read by the other kernels
+  const bool direct = plan.route == mixfp4::GemmRoute::kDirect && aligned(w_scales, 4);
+  if (workspace && plan.workspace > 0 && workspace_bytes >= plan.workspace) {
+    uint8_t* ws = static_cast<uint8_t*>(workspace);
+    if (direct) {
+      const int e =
+          launch_status(mixfp4::launch_decode_blocked(a_codes, a_scales, m, k, ws, s));
+      if (e != MIXFP4_OK) return e;
+      return launch_status(mixfp4::launch_gemm_direct(plan.tile, ws, a_tensor_scale, w_codes,
+                                                      w_scales, w_tensor_scale, m, n, k, c, s));
+    }
+    if (plan.route == mixfp4::GemmRoute::kTwoPass)
+      return launch_status(mixfp4::launch_gemm_two_pass(a_codes, a_scales, a_tensor_scale, w_codes,
+                                                        w_scales, w_tensor_scale, m, n, k, c, ws,
+                                                        s));
+  }
+  return launch_status(mixfp4::launch_gemm(a_codes, a_scales, a_tensor_scale, w_codes, w_scales,
+                                           w_tensor_scale, m, n, k, c, s));
+}
+
 int mixfp4_gemm_noalloc(const uint8_t* a_codes, const uint8_t* a_scales,
                         const float* a_tensor_scale, const uint8_t* w_codes,
                         const uint8_t* w_scales, const float* w_tensor_scale, int64_t m, int64_t n,

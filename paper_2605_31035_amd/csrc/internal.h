@@ -155,6 +155,23 @@ hipError_t launch_quantize_decode(const uint16_t* x, int64_t rows, int64_t k, in
 hipError_t launch_gemm_decoded(const uint8_t* ablk, const float* a_ts, const uint8_t* wblk,
                                const float* w_ts, int64_t m, int64_t n, int64_t k, float* c,
                                hipStream_t stream);
+// The GEMM on a decoded A (blocked layout, rows padded to 256) and a packed
+// W with 4-byte aligned scales: applies for m > 16, k % 64 == 0, k >= 256.
+// gemm_direct_tile picks the tile configuration and reports its expected
+// time in us; its result goes to launch_gemm_direct.
+bool gemm_direct_applies(int64_t m, int64_t n, int64_t k);
+int gemm_direct_tile(int64_t m, int64_t n, int64_t k, float* us);
+hipError_t launch_gemm_direct(int tile, const uint8_t* ablk, const float* a_ts,
+                              const uint8_t* w_codes, const uint8_t* w_scales, const float* w_ts,
+                              int64_t m, int64_t n, int64_t k, float* c, hipStream_t stream);
+// The route expected to be the fastest, and the workspace it needs.
+enum class GemmRoute { kNoWorkspace, kDirect, kTwoPass };
+struct GemmPlan {
+  GemmRoute route;
+  int tile;              // kDirect: the tile configuration
+  int64_t workspace;     // bytes
+};
+GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k);
 // One-launch decode step (A[m, k] bf16 row-major, quantized in the launch,
 // then C = A W^T): applies for 1 <= m <= 16 and k % 64 == 0 (the decode-
 // shape GEMM's K split); `sync` is 4 zeroed uint32 on the device, returned

@@ -373,3 +373,15 @@ def test_quantize_decode_rejects(lib):
     assert qd(out_bytes=100) == 2                   # smaller than the decoded layout
     assert qd(ts=P(0)) == 1 and qd(x=P(0)) == 1 and qd(out=P(0)) == 1 and qd(codes=P(0)) == 1
     assert qd(out=P(0x10010)) == 3 and qd(x=P(0x10008)) == 3 and qd(ts=P(0x10002)) == 3
+
+
+def test_gemm_auto_workspace(lib):
+    import ctypes
+    b = ctypes.c_int64(-1)
+    assert lib.mixfp4_gemm_auto_workspace_size(64, 4096, 4096, None) == 1
+    assert lib.mixfp4_gemm_auto_workspace_size(64, 4096, 24, ctypes.byref(b)) == 2
+    for m, n, k, want in [(16, 28672, 8192, 0), (64, 64, 48, 0), (64, 4096, 192, 0),
+                          (64, 4096, 4096, 256 * 4096 * 2),
+                          (16384, 8192, 8192, (16384 + 8192) * 8192 * 2)]:
+        assert lib.mixfp4_gemm_auto_workspace_size(m, n, k, ctypes.byref(b)) == 0
+        assert b.value == want, (m, n, k)
