@@ -185,9 +185,10 @@ __device__ __forceinline__ void to_x(uint4 r0, uint4 r1, const XDomain& xd, floa
 //
 // kSR: stochastic rounding with Philox draws per block (its global index).
 // kHad: each block is first rotated (block-diagonal Hadamard across the
-// L = b / 16 lanes holding one Hadamard block; the grid stride is a multiple
-// of 256, so a thread keeps its position in its Hadamard block and every
-// Hadamard block is processed by lanes of one wave in one iteration).
+// L = b / 16 lanes holding one Hadamard block (rotated_index); the grid
+// stride is a multiple of 256, so a thread keeps its position in its Hadamard
+// block and every Hadamard block is processed by lanes of one wave in one
+// iteration).
 template <int kDiv, bool kContig, int kMode, bool kSR, bool kHad>
 __device__ __forceinline__ void quantize_loop(const uint16_t* __restrict__ x, int64_t nbk,
                                               int64_t ldx, int64_t nblocks,
@@ -213,7 +214,10 @@ __device__ __forceinline__ void quantize_loop(const uint16_t* __restrict__ x, in
   };
   int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   SignMasks sm;
-  if constexpr (kHad) sm = load_sign_masks(hp, (int)(threadIdx.x & ((1u << hp.lanes_log2) - 1u)));
+  if constexpr (kHad) {
+    g = rotated_index(g, hp);
+    sm = load_sign_masks(hp, (int)g & ((1 << hp.lanes_log2) - 1));
+  }
   uint4 a0, a1;
   load(g, a0, a1);
   for (; g < nblocks; g += stride) {
@@ -274,12 +278,12 @@ __device__ void mixfp4_q_buffer_load_lds(mixfp4_i32x4q rsrc,
 namespace mixfp4 {
 namespace {
 
-template <int kDiv, int kMode, bool kSR, bool kHad>
+template <int kDiv, int kMode, bool kSR>
 __device__ __forceinline__ void stream_loop(const uint16_t* __restrict__ x, int64_t nblocks,
                                             uint8_t* __restrict__ codes,
                                             uint8_t* __restrict__ scales, const XDomain& xd,
                                             const ScaleRecip* tab, const SrParams& sr,
-                                            const HadamardParams& hp, uint8_t* ring) {
+                                            uint8_t* ring) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t windows = (nblocks + kWindow - 1) / kWindow;
@@ -302,8 +306,6 @@ __device__ __forceinline__ void stream_loop(const uint16_t* __restrict__ x, int6
     mixfp4_q_buffer_load_lds(r, l, 16, lane * 16, 0, 0, kRingAux);
     mixfp4_q_buffer_load_lds(r, l, 16, lane * 16, 0, 1024, kRingAux);
   };
-  SignMasks sm;
-  if constexpr (kHad) sm = load_sign_masks(hp, lane & ((1 << hp.lanes_log2) - 1));
   issue(0);
   for (int64_t i = 0; i < iters; ++i) {
     // Vector memory operations complete in issue order, and vmcnt counts
@@ -314,11 +316,10 @@ __device__ __forceinline__ void stream_loop(const uint16_t* __restrict__ x, int6
     else
       asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
     const uint4* src = reinterpret_cast<const uint4*>(slots + (i & 1) * kWindowBytes + lane * 32);
-    uint4 r0 = src[0], r1 = src[1];
+    const uint4 r0 = src[0], r1 = src[1];
     // The other slot held window i - 1, whose reads finished last iteration.
     issue(i + 1);
     const int64_t base = first_block(i);
-    if constexpr (kHad) hadamard_rotate(r0, r1, sm, hp);
     float xs[16];
     to_x<kDiv>(r0, r1, xd, xs);
     uint2 out;
@@ -369,11 +370,11 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(
   if constexpr (kContig && !kHad) {
     __shared__ __attribute__((aligned(1024))) uint8_t ring[(kThreads / 64) * 2 * kWindowBytes];
     if (two_term)
-      stream_loop<kTwoTerm, kMode, kSR, kHad>(x, nblocks, codes, scales, xd, tab, sr, hp, ring);
+      stream_loop<kTwoTerm, kMode, kSR>(x, nblocks, codes, scales, xd, tab, sr, ring);
     else if (direct)
-      stream_loop<kMarkstein, kMode, kSR, kHad>(x, nblocks, codes, scales, xd, tab, sr, hp, ring);
+      stream_loop<kMarkstein, kMode, kSR>(x, nblocks, codes, scales, xd, tab, sr, ring);
     else
-      stream_loop<kScaledX, kMode, kSR, kHad>(x, nblocks, codes, scales, xd, tab, sr, hp, ring);
+      stream_loop<kScaledX, kMode, kSR>(x, nblocks, codes, scales, xd, tab, sr, ring);
   } else {
     if (two_term)
       quantize_loop<kTwoTerm, kContig, kMode, kSR, kHad>(x, nbk, ldx, nblocks, codes, scales, xd, tab, sr,
@@ -473,9 +474,10 @@ __global__ __launch_bounds__(kThreads) void amax_rotated_kernel(
     const uint16_t* __restrict__ x, int64_t nbk, int64_t ldx, int64_t nblocks, HadamardParams hp,
     uint32_t* __restrict__ partials, uint32_t* __restrict__ out) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const SignMasks sm = load_sign_masks(hp, (int)(threadIdx.x & ((1u << hp.lanes_log2) - 1u)));
+  const int64_t g0 = rotated_index((int64_t)blockIdx.x * blockDim.x + threadIdx.x, hp);
+  const SignMasks sm = load_sign_masks(hp, (int)g0 & ((1 << hp.lanes_log2) - 1));
   uint32_t m = 0u;
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < nblocks; g += stride) {
+  for (int64_t g = g0; g < nblocks; g += stride) {
     const uint16_t* src;
     if (kContig) {
       src = x + (g << 4);
@@ -483,10 +485,9 @@ __global__ __launch_bounds__(kThreads) void amax_rotated_kernel(
       const int64_t r = g / nbk;
       src = x + r * ldx + ((g - r * nbk) << 4);
     }
-    uint4 v0 = *reinterpret_cast<const uint4*>(src);
-    uint4 v1 = *reinterpret_cast<const uint4*>(src + 8);
-    hadamard_rotate(v0, v1, sm, hp);
-    m = max(m, max(absmax8(v0), absmax8(v1)));
+    const uint4 v0 = *reinterpret_cast<const uint4*>(src);
+    const uint4 v1 = *reinterpret_cast<const uint4*>(src + 8);
+    m = max(m, hadamard_absmax(v0, v1, sm, hp));
   }
   for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
   __shared__ uint32_t wave_max[kThreads / 64];
@@ -508,8 +509,9 @@ __global__ __launch_bounds__(kThreads) void hadamard_kernel(const uint16_t* __re
                                                             int64_t nblocks, HadamardParams hp,
                                                             uint16_t* __restrict__ y) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const SignMasks sm = load_sign_masks(hp, (int)(threadIdx.x & ((1u << hp.lanes_log2) - 1u)));
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < nblocks; g += stride) {
+  const int64_t g0 = rotated_index((int64_t)blockIdx.x * blockDim.x + threadIdx.x, hp);
+  const SignMasks sm = load_sign_masks(hp, (int)g0 & ((1 << hp.lanes_log2) - 1));
+  for (int64_t g = g0; g < nblocks; g += stride) {
     const uint16_t* src;
     if (kContig) {
       src = x + (g << 4);

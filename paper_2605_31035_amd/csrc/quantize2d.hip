@@ -237,10 +237,11 @@ __global__ __launch_bounds__(kThreads2d) void quantize_t_kernel(
     uint4 v0 = *reinterpret_cast<const uint4*>(&xt[c][16 * rbl]);
     uint4 v1 = *reinterpret_cast<const uint4*>(&xt[c][16 * rbl + 8]);
     const bool valid = c0 + c < k && (r0 >> 4) + rbl < rb_total;
-    if constexpr (kHad) hadamard_rotate(v0, v1, sm, hp);
     if constexpr (kAmax) {
-      if (valid) m = max(m, max(absmax8(v0), absmax8(v1)));
+      const uint32_t bm = hadamard_absmax(v0, v1, sm, hp);
+      if (valid) m = max(m, bm);
     } else {
+      if constexpr (kHad) hadamard_rotate(v0, v1, sm, hp);
       float xs[16];
       to_fp8_domain<true>(v0, v1, sa.xmul, sa.sx, sa.rx, xs);
       const int64_t col = c0 + c, rb = (r0 >> 4) + rbl;

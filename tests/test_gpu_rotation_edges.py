@@ -1,0 +1,58 @@
+"""Rotation edges: tensors whose last row of 16 lanes holds a single Hadamard
+block, sums on bf16 midpoints (exact ties and inexact ones), and non-finite
+inputs, whose tensor scale is that of the rotated tensor."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle import hadamard as HD
+from oracle import quant as Q
+from tests._gpu import dev_bf16, host, log
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("b,rows,k", [(128, 1, 128), (128, 3, 128), (128, 5, 384), (128, 37, 640),
+                                      (64, 3, 64), (256, 3, 256), (16, 3, 48)])
+def test_rotate_then_quantize_tails(b, rows, k):
+    import paper_2605_31035_amd as M
+    rng = np.random.default_rng(rows * k)
+    # small integers: sums with few bits, many exactly halfway between two
+    # bf16 values; scaled by 2^20 in places, so that others need more than 24
+    x = rng.integers(-255, 256, (rows, k)).astype(np.float32)
+    x[:, ::7] *= np.float32(2.0 ** 20)
+    bits = W.f32_to_bf16_bits(x)
+    signs = rng.choice([-1, 1], size=b)
+    log(f"rotation tails b={b} rows={rows} k={k}")
+    sg = torch.from_numpy(signs.astype(np.int8)).cuda()
+    rot = HD.hadamard(bits, b, signs)
+    y = M.mixfp4_hadamard(dev_bf16(bits), b, sg)
+    np.testing.assert_array_equal(host(y.view(torch.int16)).view(np.uint16), rot)
+    codes, scales, s32 = M.mixfp4_quantize(dev_bf16(bits), hadamard_block=b, hadamard_signs=sg)
+    ref = Q.quantize(rot)
+    assert host(s32)[0] == ref.s32
+    np.testing.assert_array_equal(host(codes), ref.codes)
+    np.testing.assert_array_equal(host(scales), ref.scales)
+
+
+@pytest.mark.parametrize("b", [16, 64, 128])
+@pytest.mark.parametrize("transpose", [False, True])
+@pytest.mark.parametrize("bad", [[np.inf], [np.inf, -np.inf], [np.nan]])
+def test_scale_of_non_finite(b, transpose, bad):
+    """s32 is formed from max|bits| of the rotated tensor, also where an
+    infinity spreads over its block or cancels to NaN."""
+    import paper_2605_31035_amd as M
+    if transpose and b > 64:
+        pytest.skip("a transposed rotation takes at most 64 rows")
+    rng = np.random.default_rng(b)
+    x = torch.from_numpy(rng.standard_normal((256, 256)).astype(np.float32)).cuda().bfloat16()
+    for i, v in enumerate(bad):
+        x[2 * i * transpose, 2 * i] = v
+    log(f"rotation of non-finite values b={b} transpose={transpose} {bad}")
+    got = M.mixfp4_quantize(x, hadamard_block=b, transpose=transpose)[2]
+    rot = M.mixfp4_hadamard(x.t().contiguous() if transpose else x, b)
+    mag = int((rot.view(torch.int16).to(torch.int32) & 0x7FFF).max())
+    amax = torch.tensor([mag], dtype=torch.int32).to(torch.int16).view(torch.bfloat16).float()
+    want = amax / 2688 if bool(amax > 0) else torch.ones(1)
+    assert float(got) == float(want)
