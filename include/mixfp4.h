@@ -144,6 +144,27 @@ int mixfp4_quantize_ex(const uint16_t *x, int64_t rows, int64_t k, int64_t ldx,
                        uint64_t offset, void *stream);
 
 /*
+ * mixfp4_quantize_ws, mixfp4_quantize_decode_ws - mixfp4_quantize_ex and
+ * mixfp4_quantize_decode with caller-owned device scratch for the tensor-scale pass: with at least
+ * mixfp4_quantize_scratch_bytes() (4096) bytes, 4-byte aligned, the
+ * per-workgroup maxima are kept there and folded by the quantize kernel,
+ * which saves a launch.  Outputs are the same, bit for bit.  The scratch's
+ * contents on entry are ignored and on return unspecified; it must not be
+ * used by anything else until the call's work is done (same stream is
+ * enough).  scratch == NULL or less of it: as the function without _ws;
+ * misaligned: MIXFP4_ERR_ALIGN; scratch_bytes < 0: MIXFP4_ERR_SHAPE.
+ */
+int mixfp4_quantize_ws(const uint16_t *x, int64_t rows, int64_t k, int64_t ldx, uint8_t *codes,
+                       uint8_t *scales, float *tensor_scale, unsigned flags,
+                       int32_t hadamard_block, const int8_t *hadamard_signs, uint64_t seed,
+                       uint64_t offset, void *scratch, int64_t scratch_bytes, void *stream);
+int mixfp4_quantize_decode_ws(const uint16_t *x, int64_t rows, int64_t k, int64_t ldx,
+                              uint8_t *codes, uint8_t *scales, float *tensor_scale, void *out,
+                              int64_t out_bytes, unsigned flags, void *scratch,
+                              int64_t scratch_bytes, void *stream);
+int64_t mixfp4_quantize_scratch_bytes(void);
+
+/*
  * mixfp4_quantize_2d - 2D block quantization of a weight W [rows, k], as the
  * FP4 training recipe the paper follows does for weights (Sec. 3.2, Fig. 7;
  * Sec. 4.3): Algorithm 1 with the block being a 16 x 16 tile of W (one

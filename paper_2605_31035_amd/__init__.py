@@ -8,8 +8,7 @@ missing or fails to load, importing the low-level handle raises.
 Functions (same names as the C ABI in include/mixfp4.h):
   mixfp4_quantize(x, tensor_scale=None, ..., mode="mixfp4", rounding="nearest",
                   seed=0, offset=0, hadamard_block=0, hadamard_signs=None)
-      -> (codes, scales, s32)   (the C call is mixfp4_quantize_ex when
-                                  rotating or rounding stochastically)
+      -> (codes, scales, s32)   (the C call is mixfp4_quantize_ws)
   mixfp4_quantize(..., transpose=True) quantizes X^T (WGRAD operands)
   mixfp4_quantize_2d(w, tensor_scale=None, mode="mixfp4", transposed=True)
       -> (codes, scales, s32) for W and (codes_t, scales_t, s32) for W^T
@@ -143,24 +142,35 @@ def mixfp4_quantize(x: torch.Tensor, tensor_scale: torch.Tensor | None = None,
     _same_device(dev, ("x", x), ("codes", codes), ("scales", scales), ("tensor scale", ts))
     flags |= _MODES[mode]
     ldx = x.stride(0) if rows > 0 else k
-    if rounding == "nearest" and hadamard_block == 0 and not transpose:
-        st = lib.mixfp4_quantize(_ptr(x), rows, k, ldx, _ptr(codes), _ptr(scales), _ptr(ts),
-                                 flags, _stream(dev))
-    else:
-        if rounding == "stochastic":
-            flags |= STOCHASTIC
-        if transpose:
-            flags |= TRANSPOSE
-        signs = _signs_arg(hadamard_signs, hadamard_block)
-        st = lib.mixfp4_quantize_ex(_ptr(x), rows, k, ldx, _ptr(codes), _ptr(scales), _ptr(ts),
-                                    flags, hadamard_block, _ptr(signs),
-                                    seed & 0xFFFFFFFFFFFFFFFF, offset & 0xFFFFFFFFFFFFFFFF,
-                                    _stream(dev))
+    if rounding == "stochastic":
+        flags |= STOCHASTIC
+    if transpose:
+        flags |= TRANSPOSE
+    signs = _signs_arg(hadamard_signs, hadamard_block) if flags & (STOCHASTIC | TRANSPOSE) \
+        or hadamard_block else None
+    _keep, scr, scr_bytes = _scratch(rows * k if tensor_scale is None else 0, dev)
+    st = lib.mixfp4_quantize_ws(_ptr(x), rows, k, ldx, _ptr(codes), _ptr(scales), _ptr(ts),
+                                flags, hadamard_block, _ptr(signs),
+                                seed & 0xFFFFFFFFFFFFFFFF, offset & 0xFFFFFFFFFFFFFFFF,
+                                scr, scr_bytes, _stream(dev))
     _check(st)
     return codes, scales, ts
 
 
 mixfp4_quantize_ex = mixfp4_quantize
+
+_SCRATCH_WORDS = lib.mixfp4_quantize_scratch_bytes() // 4
+
+
+def _scratch(elements: int, dev):
+    """(tensor to keep, pointer, bytes) of the scratch of a tensor-scale pass
+    over so many elements (none where that pass is not a launch of its own).
+    The caching allocator may hand it out again once this call returns, which
+    the stream orders behind the launches."""
+    if elements <= 1 << 17:
+        return None, None, 0
+    t = torch.empty(_SCRATCH_WORDS, dtype=torch.int32, device=dev)
+    return t, _ptr(t), 4 * _SCRATCH_WORDS
 
 
 def _signs_arg(signs, block):
@@ -493,9 +503,10 @@ def mixfp4_quantize_decode(x: torch.Tensor, tensor_scale: torch.Tensor | None = 
     _require(ts, "tensor_scale", torch.float32, numel=1)
     _same_device(dev, ("x", x), ("codes", codes), ("scales", scales), ("tensor scale", ts),
                  ("out", out))
-    _check(lib.mixfp4_quantize_decode(_ptr(x), rows, k, x.stride(0), _ptr(codes), _ptr(scales),
-                                      _ptr(ts), _ptr(out), out.numel(), flags | _MODES[mode],
-                                      _stream(dev)))
+    _keep, scr, scr_bytes = _scratch(rows * k if tensor_scale is None else 0, dev)
+    _check(lib.mixfp4_quantize_decode_ws(_ptr(x), rows, k, x.stride(0), _ptr(codes), _ptr(scales),
+                                         _ptr(ts), _ptr(out), out.numel(), flags | _MODES[mode],
+                                         scr, scr_bytes, _stream(dev)))
     return (codes, scales, ts), Decoded(out, rows, k, ts)
 
 

@@ -32,13 +32,20 @@ int format_mode(unsigned flags) {
   return -1;
 }
 
+// The caller's scratch for per-workgroup maxima, or NULL.
+uint32_t* own_partials(void* scratch, int64_t bytes) {
+  return bytes >= (int64_t)sizeof(uint32_t) * mixfp4::kScalePartials
+             ? static_cast<uint32_t*>(scratch) : nullptr;
+}
+
 bool valid_hadamard_block(int32_t b) {
   return b == 16 || b == 32 || b == 64 || b == 128 || b == 256;
 }
 
 int quantize_impl(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8_t* codes,
                   uint8_t* scales, float* tensor_scale, unsigned flags, int32_t hadamard_block,
-                  const int8_t* hadamard_signs, uint64_t seed, uint64_t offset, void* stream) {
+                  const int8_t* hadamard_signs, uint64_t seed, uint64_t offset, void* scratch,
+                  int64_t scratch_bytes, void* stream) {
   const unsigned known = MIXFP4_SCALE_GIVEN | kModeFlags | MIXFP4_STOCHASTIC | MIXFP4_TRANSPOSE;
   if ((flags & ~known) != 0u || format_mode(flags) < 0) return MIXFP4_ERR_FLAGS;
   const bool given = (flags & MIXFP4_SCALE_GIVEN) != 0u;
@@ -63,8 +70,11 @@ int quantize_impl(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8
   if (!tensor_scale) return MIXFP4_ERR_NULL;
   const bool empty = rows == 0 || k == 0;
   if (!empty && (!x || !codes || !scales)) return MIXFP4_ERR_NULL;
-  if (!aligned(tensor_scale, 4)) return MIXFP4_ERR_ALIGN;
+  if (scratch_bytes < 0) return MIXFP4_ERR_SHAPE;
+  if (!aligned(tensor_scale, 4) || !aligned(scratch, 4)) return MIXFP4_ERR_ALIGN;
   if (!empty && (!aligned(x, 16) || !aligned(codes, 16))) return MIXFP4_ERR_ALIGN;
+  uint32_t* own = own_partials(scratch, scratch_bytes);
+  mixfp4::ScaleIn in(tensor_scale);
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();   // drop stale errors so a launch failure is ours
   if (transpose) {
@@ -76,13 +86,14 @@ int quantize_impl(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8
     if (!given) {
       const hipError_t e =
           opt.had ? mixfp4::launch_tensor_scale_t_rotated(x, rows, k, ldx, opt.hp, scales, nscr,
-                                                          tensor_scale, s)
-                  : mixfp4::launch_tensor_scale(x, rows, k, ldx, scales, nscr, tensor_scale, s);
+                                                          tensor_scale, s, own, &in)
+                  : mixfp4::launch_tensor_scale(x, rows, k, ldx, scales, nscr, tensor_scale, s,
+                                                own, &in);
       const int st = launch_status(e);
       if (st != MIXFP4_OK) return st;
     }
     return launch_status(
-        mixfp4::launch_quantize_t(x, rows, k, ldx, codes, scales, tensor_scale, opt, s));
+        mixfp4::launch_quantize_t(x, rows, k, ldx, codes, scales, in, opt, s));
   }
   if (!given && !empty && !opt.had && mixfp4::quantize_is_small(rows, k))
     return launch_status(mixfp4::launch_quantize_small(x, rows, k, ldx, codes, scales,
@@ -92,14 +103,15 @@ int quantize_impl(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8
     const hipError_t e =
         opt.had ? mixfp4::launch_tensor_scale_rotated(x, empty ? 0 : rows, k, ldx, opt.hp,
                                                       empty ? nullptr : scales, nscr,
-                                                      tensor_scale, s)
+                                                      tensor_scale, s, own, &in)
                 : mixfp4::launch_tensor_scale(x, empty ? 0 : rows, k, ldx,
-                                              empty ? nullptr : scales, nscr, tensor_scale, s);
+                                              empty ? nullptr : scales, nscr, tensor_scale, s,
+                                              own, &in);
     const int st = launch_status(e);
     if (st != MIXFP4_OK) return st;
   }
   if (empty) return MIXFP4_OK;
-  return launch_status(mixfp4::launch_quantize(x, rows, k, ldx, codes, scales, tensor_scale, opt, s));
+  return launch_status(mixfp4::launch_quantize(x, rows, k, ldx, codes, scales, in, opt, s));
 }
 
 }  // namespace
@@ -128,7 +140,7 @@ int mixfp4_quantize(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uin
   // stochastic rounding needs the seed of _ex; transposition is an _ex option
   if (flags & (MIXFP4_STOCHASTIC | MIXFP4_TRANSPOSE)) return MIXFP4_ERR_FLAGS;
   return quantize_impl(x, rows, k, ldx, codes, scales, tensor_scale, flags, 0, nullptr, 0, 0,
-                       stream);
+                       nullptr, 0, stream);
 }
 
 int mixfp4_quantize_ex(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8_t* codes,
@@ -136,7 +148,19 @@ int mixfp4_quantize_ex(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, 
                        int32_t hadamard_block, const int8_t* hadamard_signs, uint64_t seed,
                        uint64_t offset, void* stream) {
   return quantize_impl(x, rows, k, ldx, codes, scales, tensor_scale, flags, hadamard_block,
-                       hadamard_signs, seed, offset, stream);
+                       hadamard_signs, seed, offset, nullptr, 0, stream);
+}
+
+int mixfp4_quantize_ws(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8_t* codes,
+                       uint8_t* scales, float* tensor_scale, unsigned flags,
+                       int32_t hadamard_block, const int8_t* hadamard_signs, uint64_t seed,
+                       uint64_t offset, void* scratch, int64_t scratch_bytes, void* stream) {
+  return quantize_impl(x, rows, k, ldx, codes, scales, tensor_scale, flags, hadamard_block,
+                       hadamard_signs, seed, offset, scratch, scratch_bytes, stream);
+}
+
+int64_t mixfp4_quantize_scratch_bytes(void) {
+  return (int64_t)sizeof(uint32_t) * mixfp4::kScalePartials;
 }
 
 int mixfp4_quantize_2d(const uint16_t* w, int64_t rows, int64_t k, int64_t ldw, uint8_t* codes,
@@ -402,27 +426,38 @@ int mixfp4_decode_operand(const uint8_t* codes, const uint8_t* scales, int64_t r
 int mixfp4_quantize_decode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
                            uint8_t* codes, uint8_t* scales, float* tensor_scale, void* out,
                            int64_t out_bytes, unsigned flags, void* stream) {
+  return mixfp4_quantize_decode_ws(x, rows, k, ldx, codes, scales, tensor_scale, out, out_bytes,
+                                   flags, nullptr, 0, stream);
+}
+
+int mixfp4_quantize_decode_ws(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
+                              uint8_t* codes, uint8_t* scales, float* tensor_scale, void* out,
+                              int64_t out_bytes, unsigned flags, void* scratch,
+                              int64_t scratch_bytes, void* stream) {
   if ((flags & ~(MIXFP4_SCALE_GIVEN | kModeFlags)) != 0u || format_mode(flags) < 0)
     return MIXFP4_ERR_FLAGS;
   if (rows < 0 || k < 0 || (k % 32) != 0 || k > (int64_t(1) << 22)) return MIXFP4_ERR_SHAPE;
   if (rows > 0 && (ldx < k || (ldx % 8) != 0)) return MIXFP4_ERR_SHAPE;
   if (!tensor_scale) return MIXFP4_ERR_NULL;
-  if (!aligned(tensor_scale, 4)) return MIXFP4_ERR_ALIGN;
+  if (scratch_bytes < 0) return MIXFP4_ERR_SHAPE;
+  if (!aligned(tensor_scale, 4) || !aligned(scratch, 4)) return MIXFP4_ERR_ALIGN;
   const bool empty = rows == 0 || k == 0;
   if (!empty && (!x || !codes || !scales || !out)) return MIXFP4_ERR_NULL;
   if (!empty && out_bytes < mixfp4::decoded_bytes(rows, k)) return MIXFP4_ERR_SHAPE;
   if (!empty && (!aligned(x, 16) || !aligned(codes, 16) || !aligned(out, 256)))
     return MIXFP4_ERR_ALIGN;
+  mixfp4::ScaleIn in(tensor_scale);
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
   if ((flags & MIXFP4_SCALE_GIVEN) == 0u) {
     const int st = launch_status(mixfp4::launch_tensor_scale(
         x, empty ? 0 : rows, k, ldx, empty ? nullptr : scales,
-        empty ? 0 : rows * (k / mixfp4::kBlock), tensor_scale, s));
+        empty ? 0 : rows * (k / mixfp4::kBlock), tensor_scale, s,
+        own_partials(scratch, scratch_bytes), &in));
     if (st != MIXFP4_OK) return st;
   }
   if (empty) return MIXFP4_OK;
-  return launch_status(mixfp4::launch_quantize_decode(x, rows, k, ldx, codes, scales, tensor_scale,
+  return launch_status(mixfp4::launch_quantize_decode(x, rows, k, ldx, codes, scales, in,
                                                       format_mode(flags),
                                                       static_cast<uint8_t*>(out), s));
 }

@@ -100,11 +100,11 @@ template <int kMode>
 __global__ __launch_bounds__(256) void quantize_decode_kernel(
     const uint16_t* __restrict__ x, int64_t rows, int64_t k, int64_t ldx,
     uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
-    const float* __restrict__ tensor_scale, uint8_t* __restrict__ out) {
+    const ScaleIn tensor_scale, uint8_t* __restrict__ out) {
   __shared__ uint4 tile[kDecSteps * kPlane];
   __shared__ ScaleRecip tab[128];
   fill_scale_table(tab);
-  const float s32 = *tensor_scale;
+  const float s32 = load_tensor_scale(tensor_scale);
   const bool direct = s32 >= 0x1p-90f && s32 <= 0x1p120f;
   const float xmul = direct ? 1.0f : (s32 < 1.0f ? 0x1p64f : 0x1p-64f);
   const float sx = s32 * xmul, rx = __fdiv_rn(1.0f, sx);
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256) void quantize_decode_kernel(
 }  // namespace
 
 hipError_t launch_quantize_decode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
-                                  uint8_t* codes, uint8_t* scales, const float* tensor_scale,
+                                  uint8_t* codes, uint8_t* scales, const ScaleIn& tensor_scale,
                                   int mode, uint8_t* out, hipStream_t stream) {
   static ResidentCache cache{};
   const int64_t items = ((rows + kDecRows - 1) / kDecRows) * ((k / kStepK + kDecSteps - 1) / kDecSteps);

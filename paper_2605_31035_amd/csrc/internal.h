@@ -37,6 +37,20 @@ struct QuantOptions {
   HadamardParams hp{};
 };
 
+// The tensor scale of a quantize kernel: *s32 when partials is NULL,
+// otherwise formed in the kernel from `count` per-workgroup maxima of |X|
+// (bf16 magnitude bits) and stored to *out by its first workgroup.
+struct ScaleIn {
+  const float* s32;
+  const uint32_t* partials;
+  int count;
+  float* out;
+  ScaleIn(const float* p) : s32(p), partials(nullptr), count(0), out(nullptr) {}
+  ScaleIn(const uint32_t* part, int n, float* o) : s32(nullptr), partials(part), count(n), out(o) {}
+};
+// Most per-workgroup maxima a caller's scratch takes (4 KB).
+constexpr int kScalePartials = 1024;
+
 // Workgroups of `threads` threads that the device keeps resident at once for
 // `kernel` (occupancy per CU x CU count), at most max_per_cu per CU when that
 // is positive.  `cache` holds one value per device (0 = not yet known);
@@ -83,21 +97,26 @@ inline int64_t compute_units() {
 // Tensor scale s32 = max|X| / 2688 (1.0 for all-zero X) into *tensor_scale.
 // `scratch` (may be NULL) is device memory of `scratch_bytes` that the call
 // may overwrite before the quantize kernel writes it (the scale-byte output).
+// With `partials` (kScalePartials words that stay untouched until the
+// quantize kernel has run) no launch folds the maxima: *in then tells the
+// quantize kernel to do it, and otherwise to read *tensor_scale.
 hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k,
                                int64_t ldx, uint8_t* scratch, int64_t scratch_bytes,
-                               float* tensor_scale, hipStream_t stream);
+                               float* tensor_scale, hipStream_t stream,
+                               uint32_t* partials = nullptr, ScaleIn* in = nullptr);
 // Tensor scale of the rotated tensor (the amax pass of a rotate-and-quantize
 // call); same contract as launch_tensor_scale.
 hipError_t launch_tensor_scale_rotated(const uint16_t* x, int64_t rows, int64_t k,
                                        int64_t ldx, const HadamardParams& hp,
                                        uint8_t* scratch, int64_t scratch_bytes,
-                                       float* tensor_scale, hipStream_t stream);
+                                       float* tensor_scale, hipStream_t stream,
+                                       uint32_t* partials = nullptr, ScaleIn* in = nullptr);
 hipError_t launch_quantize(const uint16_t* x, int64_t rows, int64_t k,
                            int64_t ldx, uint8_t* codes, uint8_t* scales,
-                           const float* tensor_scale, const QuantOptions& opt,
+                           const ScaleIn& tensor_scale, const QuantOptions& opt,
                            hipStream_t stream);
 // Tensor scale and quantization in one launch, for tensors with
-// quantize_is_small(rows, k) (rows * k at most 2^18); rows, k > 0; no rotation.
+// quantize_is_small(rows, k) (rows * k at most 2^17); rows, k > 0; no rotation.
 bool quantize_is_small(int64_t rows, int64_t k);
 hipError_t launch_quantize_small(const uint16_t* x, int64_t rows, int64_t k,
                                  int64_t ldx, uint8_t* codes, uint8_t* scales,
@@ -113,14 +132,15 @@ hipError_t launch_quantize_2d(const uint16_t* w, int64_t n, int64_t k, int64_t l
 // [k, rows/2], scales_t [k, rows/16]; rotation (opt.had) along the rows with
 // b <= 64.
 hipError_t launch_quantize_t(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
-                             uint8_t* codes_t, uint8_t* scales_t, const float* tensor_scale,
+                             uint8_t* codes_t, uint8_t* scales_t, const ScaleIn& tensor_scale,
                              const QuantOptions& opt, hipStream_t stream);
 // s32 of the rotated X^T (COMPUTE mode with opt.had and TRANSPOSE); scratch
 // as for launch_tensor_scale.
 hipError_t launch_tensor_scale_t_rotated(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
                                          const HadamardParams& hp, uint8_t* scratch,
                                          int64_t scratch_bytes, float* tensor_scale,
-                                         hipStream_t stream);
+                                         hipStream_t stream, uint32_t* partials = nullptr,
+                                         ScaleIn* in = nullptr);
 // Standalone rotation: y [rows, k] contiguous bf16.
 hipError_t launch_hadamard(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
                            const HadamardParams& hp, uint16_t* y, hipStream_t stream);
@@ -150,7 +170,7 @@ hipError_t launch_decode_blocked(const uint8_t* codes, const uint8_t* scales, in
 // layout `out` (decoded_bytes(rows, k) bytes): codes and scales as
 // launch_quantize writes them.
 hipError_t launch_quantize_decode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
-                                  uint8_t* codes, uint8_t* scales, const float* tensor_scale,
+                                  uint8_t* codes, uint8_t* scales, const ScaleIn& tensor_scale,
                                   int mode, uint8_t* out, hipStream_t stream);
 hipError_t launch_gemm_decoded(const uint8_t* ablk, const float* a_ts, const uint8_t* wblk,
                                const float* w_ts, int64_t m, int64_t n, int64_t k, float* c,

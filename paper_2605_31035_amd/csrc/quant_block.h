@@ -24,6 +24,26 @@ __device__ __forceinline__ float tensor_scale_of(uint32_t amax_bf16_bits) {
   return amax > 0.0f ? amax / 2688.0f : 1.0f;       // Algorithm 1, first step
 }
 
+// The tensor scale of this launch (every thread of the workgroup calls it).
+// Folding up to 1024 maxima here, in every workgroup, costs less than a
+// launch of its own between the maximum pass and this one (4 KB from L2
+// against a kernel boundary): 1537 x 4096 14.6 -> 13.4 us for the two passes,
+// the transposed 2048 x 11008 55.8 -> 54.0 us.
+__device__ __forceinline__ float load_tensor_scale(const ScaleIn& in) {
+  if (!in.partials) return *in.s32;
+  __shared__ uint32_t wave_max[16];
+  uint32_t m = 0u;
+  for (int i = (int)threadIdx.x; i < in.count; i += (int)blockDim.x) m = max(m, in.partials[i]);
+  for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
+  if ((threadIdx.x & 63u) == 0u) wave_max[threadIdx.x >> 6] = m;
+  __syncthreads();
+  m = wave_max[0];
+  for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = max(m, wave_max[w]);
+  const float s32 = tensor_scale_of(m);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *in.out = s32;
+  return s32;
+}
+
 // A block-scale divisor s with its two-term reciprocal: rh = 1 / s rounded
 // toward zero and rl = fl32((1 - rh s) / s) >= 0 (the residual 1 - rh s is
 // exact: one fma).  rh + rl equals 1 / s to about 2^-48 relative.

@@ -348,10 +348,10 @@ template <bool kContig, int kMode, bool kSR, bool kHad>
 __global__ __launch_bounds__(kThreads) void quantize_kernel(
     const uint16_t* __restrict__ x, int64_t nbk, int64_t ldx, int64_t nblocks,
     uint8_t* __restrict__ codes, uint8_t* __restrict__ scales,
-    const float* __restrict__ tensor_scale, SrParams sr, HadamardParams hp) {
+    const ScaleIn tensor_scale, SrParams sr, HadamardParams hp) {
   __shared__ ScaleRecip tab[128];
   fill_scale_table(tab);
-  const float s32 = *tensor_scale;
+  const float s32 = load_tensor_scale(tensor_scale);
   const bool direct = s32 >= 0x1p-90f && s32 <= 0x1p120f;
   XDomain xd;
   xd.xmul = direct ? 1.0f : (s32 < 1.0f ? 0x1p64f : 0x1p-64f);
@@ -393,44 +393,51 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(
 // the whole tensor for max|X| (a few hundred KB, from L2 after the first), so
 // all of them hold the same s32 without talking to each other; workgroup 0
 // stores it.  The read walks blocks in the order of the quantize assignment
-// (block w * kSmallThreads + t of workgroup w goes to its thread t), so each
-// thread keeps its own block from that pass and quantizes it without a
+// (block w * kT + t of workgroup w of kT threads goes to its thread t), so
+// each thread keeps its own block from that pass and quantizes it without a
 // second read.  The maximum is order-independent: the result is the
 // two-pass one, bit for bit.
-constexpr int kSmallThreads = 1024;
-constexpr int64_t kSmallElems = int64_t(1) << 18;
+//
+// Latency-bound: one chain of read, reduce, quantize.  Workgroups as small
+// as reads of eight blocks per thread allow spread the arithmetic over the
+// CUs (up to 2048 blocks, 256 threads: one wave per SIMD, where 1024 threads
+// ran four waves behind each other), and no more loads are in flight than
+// the tensor has blocks: always eight, a one-token call read its last block
+// seven times over.  1 x 4096: 5.1 -> 2.9 us, 3 x 4096 6.6 -> 3.2, 16 x 4096
+// 6.6 -> 4.8 (one launch included).  From 2^17 elements on the maximum pass of
+// its own is faster (64 x 4096: 9.5 us here, 7.9 there).
+constexpr int64_t kSmallElems = int64_t(1) << 17;
 
-template <bool kContig, int kMode, bool kSR>
-__global__ __launch_bounds__(kSmallThreads) void quantize_small_kernel(
+template <bool kContig, int kMode, bool kSR, int kT, int kFlight>
+__global__ __launch_bounds__(kT) void quantize_small_kernel(
     const uint16_t* __restrict__ x, int64_t nbk, int64_t ldx, int64_t nblocks,
     uint8_t* __restrict__ codes, uint8_t* __restrict__ scales, float* __restrict__ tensor_scale,
     SrParams sr) {
   __shared__ ScaleRecip tab[128];
-  __shared__ uint32_t wave_max[kSmallThreads / 64];
-  fill_scale_table(tab);
+  __shared__ uint32_t wave_max[kT / 64];
   auto block_ptr = [&](int64_t g) -> const uint16_t* {
     if (kContig) return x + (g << 4);
     const int64_t r = g / nbk;
     return x + r * ldx + ((g - r * nbk) << 4);
   };
-  // max|X| as bf16 magnitude bits; eight blocks in flight per thread
-  constexpr int kInFlight = 8;
-  const int64_t rounds = (nblocks + kSmallThreads - 1) / kSmallThreads;
+  // max|X| as bf16 magnitude bits
+  const int64_t rounds = (nblocks + kT - 1) / kT;
   const int64_t mine = blockIdx.x;                  // round holding this thread's block
   uint32_t mx = 0u;
   uint4 k0 = make_uint4(0, 0, 0, 0), k1 = k0;
-  for (int64_t r0 = 0; r0 < rounds; r0 += kInFlight) {
-    uint4 v0[kInFlight], v1[kInFlight];
+  for (int64_t r0 = 0; r0 < rounds; r0 += kFlight) {
+    uint4 v0[kFlight], v1[kFlight];
 #pragma unroll
-    for (int j = 0; j < kInFlight; ++j) {
-      int64_t g = (r0 + j) * kSmallThreads + threadIdx.x;
+    for (int j = 0; j < kFlight; ++j) {
+      int64_t g = (r0 + j) * kT + threadIdx.x;
       g = g < nblocks ? g : nblocks - 1;           // past the end: re-read the last block
       const uint16_t* src = block_ptr(g);
       v0[j] = *reinterpret_cast<const uint4*>(src);
       v1[j] = *reinterpret_cast<const uint4*>(src + 8);
     }
+    if (r0 == 0) fill_scale_table(tab);             // behind the first loads
 #pragma unroll
-    for (int j = 0; j < kInFlight; ++j) {
+    for (int j = 0; j < kFlight; ++j) {
       mx = max(mx, max(absmax8(v0[j]), absmax8(v1[j])));
       if (r0 + j == mine) {
         k0 = v0[j];
@@ -443,11 +450,11 @@ __global__ __launch_bounds__(kSmallThreads) void quantize_small_kernel(
   __syncthreads();                                  // also publishes the scale table
   uint32_t r = wave_max[0];
 #pragma unroll
-  for (int w = 1; w < kSmallThreads / 64; ++w) r = max(r, wave_max[w]);
+  for (int w = 1; w < kT / 64; ++w) r = max(r, wave_max[w]);
   const float s32 = tensor_scale_of(r);
   if (blockIdx.x == 0 && threadIdx.x == 0) *tensor_scale = s32;
 
-  const int64_t g = mine * kSmallThreads + threadIdx.x;
+  const int64_t g = mine * kT + threadIdx.x;
   if (g >= nblocks) return;
   const bool direct = s32 >= 0x1p-90f && s32 <= 0x1p120f;
   float xs[16];
@@ -539,9 +546,19 @@ int grid_for(int64_t work, int per_thread) {
 // the quantize kernel overwrites afterwards) when it holds at least 16 slots,
 // else an atomic on *tensor_scale.  `run(grid, partials, out)` launches the
 // maximum kernel; `grid` is capped by the slots.
+// With the caller's own `own` words nothing is folded here: *in hands them to
+// the quantize kernel.
 template <typename Run>
 hipError_t tensor_scale_with(int64_t work, int grid, uint8_t* scratch, int64_t scratch_bytes,
-                             float* tensor_scale, hipStream_t stream, Run run) {
+                             float* tensor_scale, hipStream_t stream, uint32_t* own, ScaleIn* in,
+                             Run run) {
+  if (in) *in = ScaleIn(tensor_scale);
+  if (work > 0 && own && in) {
+    if (grid > kScalePartials) grid = kScalePartials;
+    run(grid, own, (uint32_t*)nullptr);
+    *in = ScaleIn(own, grid, tensor_scale);
+    return hipGetLastError();
+  }
   const uintptr_t base = reinterpret_cast<uintptr_t>(scratch);
   const uintptr_t aligned = (base + 3u) & ~uintptr_t(3);
   const int64_t slots = scratch ? (scratch_bytes - (int64_t)(aligned - base)) / 4 : 0;
@@ -576,7 +593,7 @@ HadamardParams hadamard_params(int b, const int8_t* signs) {
 
 hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
                                uint8_t* scratch, int64_t scratch_bytes, float* tensor_scale,
-                               hipStream_t stream) {
+                               hipStream_t stream, uint32_t* own, ScaleIn* in) {
   const int64_t total = rows * (k >> 3);
   if (ldx == k) {
     // one window of 4 KB per wave, four waves per workgroup, at most 4
@@ -585,7 +602,7 @@ hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k, int64
     const int64_t wanted = (total + 4 * kAmaxWindow - 1) / (4 * kAmaxWindow);
     const int64_t resident = resident_groups(amax_stream_kernel, cache, 4);
     const int g = (int)(wanted < resident ? (wanted > 0 ? wanted : 1) : resident);
-    return tensor_scale_with(total, g, scratch, scratch_bytes, tensor_scale, stream,
+    return tensor_scale_with(total, g, scratch, scratch_bytes, tensor_scale, stream, own, in,
                              [&](int grid, uint32_t* partials, uint32_t* out) {
                                amax_stream_kernel<<<grid, kThreads, 0, stream>>>(x, total,
                                                                                   partials, out);
@@ -594,7 +611,7 @@ hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k, int64
   // up to 1024 workgroups x 256 threads x 4 loads of 16 B keeps ~16 MB in flight
   int g = grid_for(total, 4);
   if (g > 1024) g = 1024;
-  return tensor_scale_with(total, g, scratch, scratch_bytes, tensor_scale, stream,
+  return tensor_scale_with(total, g, scratch, scratch_bytes, tensor_scale, stream, own, in,
                            [&](int grid, uint32_t* partials, uint32_t* out) {
                              amax_kernel<<<grid, kThreads, 0, stream>>>(x, rows, k, ldx, partials,
                                                                          out);
@@ -604,7 +621,7 @@ hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k, int64
 hipError_t launch_tensor_scale_rotated(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
                                        const HadamardParams& hp, uint8_t* scratch,
                                        int64_t scratch_bytes, float* tensor_scale,
-                                       hipStream_t stream) {
+                                       hipStream_t stream, uint32_t* own, ScaleIn* in) {
   const int64_t nbk = k / kBlock, nblocks = rows * nbk;
   static ResidentCache cache_c, cache_s;
   const int64_t resident = ldx == k ? resident_groups(amax_rotated_kernel<true>, cache_c)
@@ -612,7 +629,7 @@ hipError_t launch_tensor_scale_rotated(const uint16_t* x, int64_t rows, int64_t 
   const int64_t wanted = (nblocks + kThreads - 1) / kThreads;
   int g = (int)(wanted < resident ? wanted : resident);
   if (g < 1) g = 1;
-  return tensor_scale_with(nblocks, g, scratch, scratch_bytes, tensor_scale, stream,
+  return tensor_scale_with(nblocks, g, scratch, scratch_bytes, tensor_scale, stream, own, in,
                            [&](int grid, uint32_t* partials, uint32_t* out) {
                              if (ldx == k)
                                amax_rotated_kernel<true><<<grid, kThreads, 0, stream>>>(
@@ -625,24 +642,40 @@ hipError_t launch_tensor_scale_rotated(const uint16_t* x, int64_t rows, int64_t 
 
 namespace {
 
+template <int kMode, bool kSR, int kT, int kFlight>
+void launch_small_kernel(const uint16_t* x, int64_t nbk, int64_t ldx, int64_t nblocks, bool contig,
+                         uint8_t* codes, uint8_t* scales, float* tensor_scale, const SrParams& sr,
+                         hipStream_t stream) {
+  const int64_t g = (nblocks + kT - 1) / kT;   // one block per thread
+  if (contig)
+    quantize_small_kernel<true, kMode, kSR, kT, kFlight><<<(unsigned)g, kT, 0, stream>>>(
+        x, nbk, ldx, nblocks, codes, scales, tensor_scale, sr);
+  else
+    quantize_small_kernel<false, kMode, kSR, kT, kFlight><<<(unsigned)g, kT, 0, stream>>>(
+        x, nbk, ldx, nblocks, codes, scales, tensor_scale, sr);
+}
+
 template <int kMode, bool kSR>
 hipError_t launch_small_mode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
                              uint8_t* codes, uint8_t* scales, float* tensor_scale,
                              const SrParams& sr, hipStream_t stream) {
   const int64_t nbk = k / kBlock, nblocks = rows * nbk;
-  const int64_t g = (nblocks + kSmallThreads - 1) / kSmallThreads;   // one block per thread
-  if (ldx == k)
-    quantize_small_kernel<true, kMode, kSR><<<(unsigned)g, kSmallThreads, 0, stream>>>(
-        x, nbk, ldx, nblocks, codes, scales, tensor_scale, sr);
-  else
-    quantize_small_kernel<false, kMode, kSR><<<(unsigned)g, kSmallThreads, 0, stream>>>(
-        x, nbk, ldx, nblocks, codes, scales, tensor_scale, sr);
+  const bool contig = ldx == k;
+#define MIXFP4_SMALL(KT, KFLIGHT)                                                               \
+  launch_small_kernel<kMode, kSR, KT, KFLIGHT>(x, nbk, ldx, nblocks, contig, codes, scales,     \
+                                               tensor_scale, sr, stream)
+  if (nblocks <= 256) MIXFP4_SMALL(256, 1);
+  else if (nblocks <= 1024) MIXFP4_SMALL(256, 4);
+  else if (nblocks <= 2048) MIXFP4_SMALL(256, 8);
+  else if (nblocks <= 4096) MIXFP4_SMALL(512, 8);
+  else MIXFP4_SMALL(1024, 8);
+#undef MIXFP4_SMALL
   return hipGetLastError();
 }
 
 template <int kMode, bool kSR, bool kHad>
 hipError_t launch_mode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8_t* codes,
-                       uint8_t* scales, const float* tensor_scale, const QuantOptions& opt,
+                       uint8_t* scales, const ScaleIn& tensor_scale, const QuantOptions& opt,
                        hipStream_t stream) {
   const int64_t nbk = k / kBlock;
   const int64_t nblocks = rows * nbk;
@@ -690,7 +723,7 @@ hipError_t launch_mode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, 
 
 template <int kMode>
 hipError_t launch_mode_opts(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
-                            uint8_t* codes, uint8_t* scales, const float* tensor_scale,
+                            uint8_t* codes, uint8_t* scales, const ScaleIn& tensor_scale,
                             const QuantOptions& opt, hipStream_t stream) {
   if (opt.sr)
     return opt.had ? launch_mode<kMode, true, true>(x, rows, k, ldx, codes, scales, tensor_scale,
@@ -730,7 +763,7 @@ hipError_t launch_quantize_small(const uint16_t* x, int64_t rows, int64_t k, int
 bool quantize_is_small(int64_t rows, int64_t k) { return rows * k <= kSmallElems; }
 
 hipError_t launch_quantize(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
-                           uint8_t* codes, uint8_t* scales, const float* tensor_scale,
+                           uint8_t* codes, uint8_t* scales, const ScaleIn& tensor_scale,
                            const QuantOptions& opt, hipStream_t stream) {
   if (rows * (k / kBlock) == 0) return hipSuccess;
   if (opt.mode == kFourSix)

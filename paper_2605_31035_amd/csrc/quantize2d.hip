@@ -201,14 +201,14 @@ template <int kMode, bool kSR, bool kHad, bool kAmax>
 __global__ __launch_bounds__(kThreads2d) void quantize_t_kernel(
     const uint16_t* __restrict__ x, int64_t rows, int64_t k, int64_t ldx,
     uint8_t* __restrict__ codes_t, uint8_t* __restrict__ scales_t,
-    const float* __restrict__ tensor_scale, SrParams sr, HadamardParams hp,
+    const ScaleIn tensor_scale, SrParams sr, HadamardParams hp,
     uint32_t* __restrict__ partials) {
   __shared__ ScaleRecip tab[128];
   __shared__ uint16_t xt[kTileC][kPitch];
   __shared__ uint32_t wave_max[kThreads2d / 64];
   if constexpr (!kAmax) fill_scale_table(tab);
   ScaleArgs sa{1.0f, 1.0f, 1.0f};
-  if constexpr (!kAmax) sa = scale_args(*tensor_scale);
+  if constexpr (!kAmax) sa = scale_args(load_tensor_scale(tensor_scale));
   SignMasks sm;
   if constexpr (kHad) sm = load_sign_masks(hp, (int)(threadIdx.x & ((1u << hp.lanes_log2) - 1u)));
   const int64_t trs = (rows + kTileR - 1) / kTileR, tcs = (k + kTileC - 1) / kTileC;
@@ -311,7 +311,7 @@ hipError_t launch_2d_mode(const uint16_t* w, int64_t n, int64_t k, int64_t ldw, 
 
 template <int kMode, bool kSR, bool kHad>
 hipError_t launch_t_mode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
-                         uint8_t* codes_t, uint8_t* scales_t, const float* tensor_scale,
+                         uint8_t* codes_t, uint8_t* scales_t, const ScaleIn& tensor_scale,
                          const QuantOptions& opt, hipStream_t stream) {
   const int64_t tiles = ((rows + kTileR - 1) / kTileR) * ((k + kTileC - 1) / kTileC);
   const int g = grid_2d(tiles, 1);
@@ -322,7 +322,7 @@ hipError_t launch_t_mode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx
 
 template <int kMode>
 hipError_t launch_t_opts(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
-                         uint8_t* codes_t, uint8_t* scales_t, const float* tensor_scale,
+                         uint8_t* codes_t, uint8_t* scales_t, const ScaleIn& tensor_scale,
                          const QuantOptions& opt, hipStream_t stream) {
   if (opt.sr)
     return opt.had ? launch_t_mode<kMode, true, true>(x, rows, k, ldx, codes_t, scales_t,
@@ -352,7 +352,7 @@ hipError_t launch_quantize_2d(const uint16_t* w, int64_t n, int64_t k, int64_t l
 }
 
 hipError_t launch_quantize_t(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
-                             uint8_t* codes_t, uint8_t* scales_t, const float* tensor_scale,
+                             uint8_t* codes_t, uint8_t* scales_t, const ScaleIn& tensor_scale,
                              const QuantOptions& opt, hipStream_t stream) {
   if (rows == 0 || k == 0) return hipSuccess;
   if (opt.mode == 3)
@@ -367,7 +367,7 @@ hipError_t launch_quantize_t(const uint16_t* x, int64_t rows, int64_t k, int64_t
 hipError_t launch_tensor_scale_t_rotated(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
                                          const HadamardParams& hp, uint8_t* scratch,
                                          int64_t scratch_bytes, float* tensor_scale,
-                                         hipStream_t stream) {
+                                         hipStream_t stream, uint32_t* own, ScaleIn* in) {
   // per-workgroup maxima in the caller's scale-byte output (>= 1 slot per
   // workgroup: rows * k / 16 bytes hold at least one 4-byte slot per 64 x 64 tile)
   const int64_t tiles = ((rows + kTileR - 1) / kTileR) * ((k + kTileC - 1) / kTileC);
@@ -375,6 +375,14 @@ hipError_t launch_tensor_scale_t_rotated(const uint16_t* x, int64_t rows, int64_
   const uintptr_t aligned = (base + 3u) & ~uintptr_t(3);
   const int64_t slots = (scratch_bytes - (int64_t)(aligned - base)) / 4;
   int g = grid_2d(tiles, 1);
+  if (in) *in = ScaleIn(tensor_scale);
+  if (own && in) {
+    if (g > kScalePartials) g = kScalePartials;
+    quantize_t_kernel<0, false, true, true><<<g, kThreads2d, 0, stream>>>(
+        x, rows, k, ldx, nullptr, nullptr, nullptr, SrParams{}, hp, own);
+    *in = ScaleIn(own, g, tensor_scale);
+    return hipGetLastError();
+  }
   if (g > slots) g = (int)slots;
   if (g < 1) return hipErrorInvalidValue;
   uint32_t* partials = reinterpret_cast<uint32_t*>(aligned);
