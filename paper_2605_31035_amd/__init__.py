@@ -2,7 +2,10 @@
 
 The binding only marshals arguments: torch supplies device memory and the
 current HIP stream, every step of the quantizer, dequantizer and GEMM runs in
-the library's HIP kernels.  There is no CPU fallback: if the library is
+the library's HIP kernels.  The per-layer calls with outputs allocated here
+go through one native call (csrc/binding.cpp); it declines arguments that it
+does not take as they are, and the Python code below then checks and names
+what is wrong, or marshals them itself.  There is no CPU fallback: if the library is
 missing or fails to load, importing the low-level handle raises.
 
 Functions (same names as the C ABI in include/mixfp4.h):
@@ -30,7 +33,7 @@ from typing import NamedTuple
 
 import torch
 
-from ._lib import LIB_PATH, MixFP4Error, lib
+from ._lib import LIB_PATH, MixFP4Error, lib, native
 
 __all__ = ["mixfp4_decode_step", "decode_step_applies", "gemm_two_pass_preferred", "mixfp4_quantize", "mixfp4_quantize_ex", "mixfp4_hadamard", "mixfp4_dequantize",
            "mixfp4_gemm", "MixFP4Error", "LIB_PATH", "lib", "SCALE_COMPUTE", "SCALE_GIVEN",
@@ -118,6 +121,14 @@ def mixfp4_quantize(x: torch.Tensor, tensor_scale: torch.Tensor | None = None,
         raise ValueError(f"mode must be one of {sorted(_MODES)}")
     if rounding not in ("nearest", "stochastic"):
         raise ValueError("rounding must be 'nearest' or 'stochastic'")
+    if codes is None and scales is None and scale_out is None:
+        r = native.quantize(x, tensor_scale,
+                            (SCALE_COMPUTE if tensor_scale is None else SCALE_GIVEN) | _MODES[mode]
+                            | (STOCHASTIC if rounding == "stochastic" else 0)
+                            | (TRANSPOSE if transpose else 0),
+                            hadamard_block, hadamard_signs, seed, offset)
+        if r is not None:
+            return r
     if x.dtype != torch.bfloat16 or x.dim() != 2:
         raise ValueError("x must be a 2-D bfloat16 CUDA tensor")
     if x.stride(1) != 1:
@@ -237,6 +248,9 @@ def mixfp4_dequantize(codes: torch.Tensor, scales: torch.Tensor,
                       tensor_scale: torch.Tensor | None = None) -> torch.Tensor:
     """Decode MixFP4 to fp32 [rows, k]; ``tensor_scale`` None decodes in the
     FP8 domain (s32 = 1)."""
+    r = native.dequantize(codes, scales, tensor_scale)
+    if r is not None:
+        return r
     if not isinstance(codes, torch.Tensor) or codes.dim() != 2:
         raise ValueError("codes must be a 2-D uint8 tensor [rows, k/2]")
     rows, half = codes.shape
@@ -348,6 +362,10 @@ def mixfp4_gemm(a, w, out: torch.Tensor | None = None, workspace=None) -> torch.
     True (mixfp4_gemm_ws with a workspace of mixfp4_gemm_workspace_size bytes
     allocated here), or "auto" (mixfp4_gemm_auto: the route expected to be
     the fastest, with the workspace it needs allocated here)."""
+    if out is None and (workspace is None or isinstance(workspace, str) and workspace == "auto"):
+        r = native.gemm(a, w, workspace is not None)
+        if r is not None:
+            return r
     ac, asc, ats = a
     wc, wsc, wts = w
     for name, t in (("A codes", ac), ("W codes", wc)):
@@ -416,6 +434,11 @@ def mixfp4_decode_step(x: torch.Tensor, w, out: torch.Tensor | None = None, a_ou
     int32 on the device that the launch leaves zeroed; default, one per
     device kept by this module (calls on one device must then be ordered,
     e.g. on one stream)."""
+    if out is None and a_out is None and isinstance(x, torch.Tensor):
+        s = sync if sync is not None else _STEP_SYNC.get((x.device.type, x.device.index))
+        r = native.decode_step(x, w, s) if s is not None else None
+        if r is not None:
+            return r
     if not isinstance(x, torch.Tensor) or x.dim() != 2 or x.dtype != torch.bfloat16:
         raise ValueError("x must be a 2-D bfloat16 tensor")
     wc, wsc, wts = w

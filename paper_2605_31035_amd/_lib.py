@@ -89,3 +89,6 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
 
 
 lib = load()
+
+# the native call path (csrc/binding.cpp), linked against the same library
+from . import _native as native  # noqa: E402,F401

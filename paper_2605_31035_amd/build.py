@@ -3,6 +3,9 @@
 Usage: python paper_2605_31035_amd/build.py   (or call build(); importing the
 package first would load the library being rebuilt).
 
+Two libraries are built: libmixfp4.so (the C ABI and its kernels) and
+_native.so (the binding's native call path, which links it and torch).
+
 Every HIP source is compiled for gfx950 only, with fp contraction off (the
 quantizer relies on exact IEEE operations in the order written) and packed
 fp32 instructions disabled.  The shared library lands next to this file so
@@ -21,6 +24,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmixfp4.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.cpp", "quantize.hip", "quantize2d.hip", "dequantize.hip", "gemm.hip",
            "gemm_f16.hip", "gemm_direct.hip", "decode_operand.hip", "quantize_variant.hip"]
 
@@ -47,6 +51,20 @@ def _run(cmd):
     return err
 
 
+def _build_native(obj: str) -> None:
+    """Compile csrc/binding.cpp against torch (host code only)."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    inc = [os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           sysconfig.get_paths()["include"], os.path.join(ROCM, "include"),
+           os.path.join(ROOT, "include")]
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+          *[f"-isystem{d}" for d in inc], "-c", os.path.join(CSRC, "binding.cpp"), "-o", obj])
+
+
 def build(verbose: bool = False) -> str:
     """Compile every source and link libmixfp4.so; return its path."""
     if not os.path.exists(HIPCC):
@@ -62,12 +80,22 @@ def build(verbose: bool = False) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(len(SOURCES)) as ex:
+    native_obj = os.path.join(BUILD, "binding.o")
+    with ThreadPoolExecutor(len(SOURCES) + 1) as ex:
+        native = ex.submit(_build_native, native_obj)
         objs = list(ex.map(compile_one, SOURCES))
+        native.result()
     tmp = LIB + ".tmp"
     _run([HIPCC, "-shared", "-fPIC", f"--offload-arch={ARCH}", "-o", tmp, *objs,
           f"-Wl,-rpath,{os.path.join(ROCM, 'lib')}"])
     shutil.move(tmp, LIB)
+    import torch
+    tlib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    tmp = NATIVE + ".tmp"
+    _run(["g++", "-shared", "-fPIC", "-o", tmp, native_obj, f"-L{HERE}", "-l:libmixfp4.so",
+          f"-L{tlib}", "-ltorch_python",
+          "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN", f"-Wl,-rpath,{tlib}"])
+    shutil.move(tmp, NATIVE)
     return LIB
 
 
