@@ -293,8 +293,8 @@ __device__ __forceinline__ void encode_i_saturated(const float (&xs)[16], const 
 // reads: up iff w > 511 - 2u, ties (w == 511 - 2u) to the even code.  y at
 // or above the largest magnitude clamps to code 7.  E2M1 spacing: 1/2 below
 // 2, 1 below 4, 2 up to 6; E1M2 (x2): 1 everywhere.
-__device__ __forceinline__ uint2 sr_codes(const float (&xs)[16], const ScaleRecip& sc, bool int4,
-                                          uint4 rnd) {
+__device__ __forceinline__ uint2 sr_codes_ties(const float (&xs)[16], const ScaleRecip& sc,
+                                               bool int4, uint4 rnd) {
   const uint32_t words[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
   // Branch-free lattice choice (a per-lane select, not control flow): E2M1
   // spacing 2^(t-1) with t = clamp(exponent of y, 0, 2), so z = y 2^(1-t)
@@ -321,6 +321,53 @@ __device__ __forceinline__ uint2 sr_codes(const float (&xs)[16], const ScaleReci
     o[j >> 3] |= (code | (neg << 3)) << (4 * (j & 7));
   }
   return make_uint2(o[0], o[1]);
+}
+
+// The same codes in fixed point, for blocks without a tie.  In units of
+// 2^-22 of the lattice step the rule is code = floor(z + (2u + 1) / 512)
+// except at w == 511 - 2u exactly: the position z of y on the lattice is an
+// integer B with 22 fraction bits, to which (2u + 1) << 13 is added.
+//   E2M1: below 2, z = 2 y, so B = trunc(2^23 y); from 1 on the lattice is
+//   that of a float with one mantissa bit, and B is the bit pattern of 2^23 y
+//   less a constant (both agree on [1, 2)).
+//   E1M2 (x2): z = y, B = trunc(2^22 y) (bit pattern from y = 16 on, where
+//   only the clamp to 7 is left).
+// The scaled reciprocals give 2^23 y or 2^22 y directly, and the clamp at the
+// largest magnitude is the code's.  A sum with zero fraction bits may be a
+// tie (or hide bits that trunc dropped): the few lanes that see one redo the
+// block.  `sign`: bit 3 of every nibble of a negative X.  About 15
+// instructions per element against 30; 2^28 elements, s32 given: 334 -> 242 us.
+__device__ __forceinline__ uint2 sr_codes(const float (&xs)[16], const ScaleRecip& sc, bool int4,
+                                          uint4 rnd, uint2 sign) {
+  const float up = int4 ? 0x1p22f : 0x1p23f;
+  const float rh = sc.rh * up, rl = sc.rl * up;
+  const float linear = int4 ? 0x1p26f : 0x1p24f;      // trunc below, bit pattern from here on
+  const uint32_t words[4] = {rnd.x, rnd.y, rnd.z, rnd.w};
+  uint32_t o[2] = {0u, 0u};
+  uint32_t low = 0xFFFFFFFFu;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    // draws of four elements, inverted (255 - u) where X is negative: the
+    // sign of each x replicated into its byte
+    const uint32_t x0 = __float_as_uint(xs[4 * q]), x1 = __float_as_uint(xs[4 * q + 1]);
+    const uint32_t x2 = __float_as_uint(xs[4 * q + 2]), x3 = __float_as_uint(xs[4 * q + 3]);
+    const uint32_t u4 = words[q] ^ __builtin_amdgcn_perm(x1, x0, 0x0C0C0B09u) ^
+                        __builtin_amdgcn_perm(x3, x2, 0x0B090C0Cu);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int j = 4 * q + e;
+      const float yk = div_scale(fabsf(xs[j]), rh, rl);
+      const uint32_t fixed = (uint32_t)yk;
+      const uint32_t coded = __float_as_uint(yk) - 0x4A800000u;
+      const uint32_t base = yk < linear ? fixed : coded;
+      const uint32_t u = (e < 2 ? u4 << (14 - 8 * e) : u4 >> (8 * e - 14)) & 0x3FC000u;
+      const uint32_t sum = base + u + 0x2000u;
+      low = min(low, sum << 10);
+      o[j >> 3] |= min(sum >> 22, 7u) << (4 * (j & 7));
+    }
+  }
+  if (low == 0u) return sr_codes_ties(xs, sc, int4, rnd);
+  return make_uint2(o[0] | sign.x, o[1] | sign.y);
 }
 
 // 4/6: both candidates are E2M1, under E4M3(bm/6) and E4M3(bm/4) (bm/4 is
@@ -389,7 +436,8 @@ __device__ __forceinline__ void quantize_four_six(const float (&xs)[16], float b
     use4 = d > 0.0;
   }
   if constexpr (kSR)
-    out = sr_codes(xs, use4 ? e4 : e6, false, rnd);
+    out = sr_codes(xs, use4 ? e4 : e6, false, rnd,
+                   make_uint2(p6[0] & 0x88888888u, p6[1] & 0x88888888u));
   else
     out = use4 ? make_uint2(p4[0], p4[1]) : make_uint2(p6[0], p6[1]);
   scale_byte = use4 ? c4 : c6;
@@ -443,7 +491,9 @@ __device__ __forceinline__ void quantize_xs(const float (&xs)[16], const ScaleRe
     encode_f_pair<14>(xs, ef, pf);
   }
   if constexpr (kMode == kForceE2M1) {
-    out = kSR ? sr_codes(xs, ef, false, rnd) : make_uint2(pf[0], pf[1]);
+    out = kSR ? sr_codes(xs, ef, false, rnd,
+                         make_uint2(pf[0] & 0x88888888u, pf[1] & 0x88888888u))
+              : make_uint2(pf[0], pf[1]);
     scale_byte = cf;
     return;
   }
@@ -470,7 +520,8 @@ __device__ __forceinline__ void quantize_xs(const float (&xs)[16], const ScaleRe
     uint32_t sg[2] = {0u, 0u};
 #pragma unroll
     for (int j = 0; j < 16; ++j) sg[j >> 3] |= (__float_as_uint(xs[j]) >> 31) << (4 * (j & 7) + 3);
-    out = kSR ? sr_codes(xs, ei, true, rnd) : make_uint2(pi[0] | sg[0], pi[1] | sg[1]);
+    out = kSR ? sr_codes(xs, ei, true, rnd, make_uint2(sg[0], sg[1]))
+              : make_uint2(pi[0] | sg[0], pi[1] | sg[1]);
     scale_byte = 0x80u | ci;
     return;
   }
@@ -540,7 +591,8 @@ __device__ __forceinline__ void quantize_xs(const float (&xs)[16], const ScaleRe
   }
   // Sign of X into bit 3 of every nibble: the E2M1 codes already carry it.
   if constexpr (kSR) {
-    out = sr_codes(xs, t1 ? ei : ef, t1, rnd);
+    out = sr_codes(xs, t1 ? ei : ef, t1, rnd,
+                   make_uint2(pf[0] & 0x88888888u, pf[1] & 0x88888888u));
   } else {
     out.x = t1 ? (pi[0] | (pf[0] & 0x88888888u)) : pf[0];
     out.y = t1 ? (pi[1] | (pf[1] & 0x88888888u)) : pf[1];
