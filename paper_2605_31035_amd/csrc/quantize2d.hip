@@ -191,11 +191,19 @@ __global__ __launch_bounds__(kThreads2d) void quantize_2d_both_kernel(
 // transposed (column-major), then thread t owns column c = t / 4 and row
 // block t % 4 of the tile: its 16 values are the X^T block (c, row block),
 // read as two 16-byte vectors, exactly the input of the 1D block code.  A
+// thread stages 8 columns of two adjacent rows, one dword of two values per
+// column; the 16-byte pieces of a column sit XOR-swizzled by its group of 8,
+// so that the writes of a wave (8 groups x 8 row pairs) and the reads are at
+// most two to a bank.  Staged value by value into padded columns, the 16-bit
+// writes met four to a bank and cost as much as the quantizer's arithmetic:
+// rotated X^T of 2048 x 11008 with its scale 54.0 -> 45.5 us.  A
 // Hadamard block of b = 16 L rows spans the L lanes of a quad.  Blocks of
 // X^T are numbered g = column * rows/16 + row block (the stochastic-rounding
 // counter), as in the 1D layout of X^T.  kAmax: only max|rotated X| per
 // workgroup (COMPUTE mode with a rotation).
-constexpr int kTileR = 64, kTileC = 64, kPitch = kTileR + 8;   // LDS row pitch (elements)
+constexpr int kTileR = 64, kTileC = 64;
+constexpr int kPieces = kTileR / 8;                // 16-byte pieces of a staged column
+__device__ __forceinline__ int piece_of(int c, int i) { return c * kPieces + (i ^ ((c >> 3) & 7)); }
 
 template <int kMode, bool kSR, bool kHad, bool kAmax>
 __global__ __launch_bounds__(kThreads2d) void quantize_t_kernel(
@@ -204,7 +212,7 @@ __global__ __launch_bounds__(kThreads2d) void quantize_t_kernel(
     const ScaleIn tensor_scale, SrParams sr, HadamardParams hp,
     uint32_t* __restrict__ partials) {
   __shared__ ScaleRecip tab[128];
-  __shared__ uint16_t xt[kTileC][kPitch];
+  __shared__ uint4 xt[kTileC * kPieces];
   __shared__ uint32_t wave_max[kThreads2d / 64];
   if constexpr (!kAmax) fill_scale_table(tab);
   ScaleArgs sa{1.0f, 1.0f, 1.0f};
@@ -219,23 +227,24 @@ __global__ __launch_bounds__(kThreads2d) void quantize_t_kernel(
     const int64_t tr0 = tile / tcs, tc0 = tile - tr0 * tcs;
     const int64_t r0 = tr0 * kTileR, c0 = tc0 * kTileC;
     __syncthreads();                         // previous tile's reads are done (and the table is built)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int q = threadIdx.x + kThreads2d * h;
-      const int row = q >> 3, ch = q & 7;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (r0 + row < rows && c0 + 8 * ch < k)
-        v = *reinterpret_cast<const uint4*>(x + (r0 + row) * ldx + c0 + 8 * ch);
-      const uint32_t e[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        xt[8 * ch + 2 * j][row] = (uint16_t)e[j];
-        xt[8 * ch + 2 * j + 1][row] = (uint16_t)(e[j] >> 16);
+    {
+      const int p = threadIdx.x >> 3, ch = threadIdx.x & 7;    // row pair, group of 8 columns
+      uint4 a = make_uint4(0, 0, 0, 0), b = a;
+      if (r0 + 2 * p < rows && c0 + 8 * ch < k) {              // rows % 16 == 0: both or neither
+        const uint16_t* src = x + (r0 + 2 * p) * ldx + c0 + 8 * ch;
+        a = *reinterpret_cast<const uint4*>(src);
+        b = *reinterpret_cast<const uint4*>(src + ldx);
       }
+      const uint32_t ea[4] = {a.x, a.y, a.z, a.w}, eb[4] = {b.x, b.y, b.z, b.w};
+      uint32_t* words = reinterpret_cast<uint32_t*>(xt);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        words[4 * piece_of(8 * ch + i, p >> 2) + (p & 3)] =
+            __builtin_amdgcn_perm(eb[i >> 1], ea[i >> 1], (i & 1) ? 0x07060302u : 0x05040100u);
     }
     __syncthreads();
-    uint4 v0 = *reinterpret_cast<const uint4*>(&xt[c][16 * rbl]);
-    uint4 v1 = *reinterpret_cast<const uint4*>(&xt[c][16 * rbl + 8]);
+    uint4 v0 = xt[piece_of(c, 2 * rbl)];
+    uint4 v1 = xt[piece_of(c, 2 * rbl + 1)];
     const bool valid = c0 + c < k && (r0 >> 4) + rbl < rb_total;
     if constexpr (kAmax) {
       const uint32_t bm = hadamard_absmax(v0, v1, sm, hp);
