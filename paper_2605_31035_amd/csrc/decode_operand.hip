@@ -92,10 +92,10 @@ __global__ __launch_bounds__(256) void decode_blocked_kernel(const uint8_t* __re
 // them as two blocks with the quantizer's per-block code (quantize_xs: the
 // codes, scales and format bits are mixfp4_quantize's), stores the 16 code
 // bytes and two scale bytes, and decodes its own codes into the LDS tile
-// that leaves as eight 2 KB runs.  x = fl32(X / s32) takes Markstein's step
-// (exact for every tensor scale, with X and s32 rescaled by 2^+-64 outside
-// [2^-90, 2^120]).  Measured on A[16384, 8192]: about 120 us, against 76 us
-// for the quantizer and 72 us for the decode pass run one after the other.
+// that leaves as eight 2 KB runs.  VALU-bound: x = fl32(X / s32) takes the
+// two-term division where s32 allows it (127.7 -> 124 us on A[16384, 8192]
+// against Markstein's step; the quantizer and the decode pass one after the
+// other take 148).
 template <int kMode>
 __global__ __launch_bounds__(256) void quantize_decode_kernel(
     const uint16_t* __restrict__ x, int64_t rows, int64_t k, int64_t ldx,
@@ -105,9 +105,8 @@ __global__ __launch_bounds__(256) void quantize_decode_kernel(
   __shared__ ScaleRecip tab[128];
   fill_scale_table(tab);
   const float s32 = load_tensor_scale(tensor_scale);
-  const bool direct = s32 >= 0x1p-90f && s32 <= 0x1p120f;
-  const float xmul = direct ? 1.0f : (s32 < 1.0f ? 0x1p64f : 0x1p-64f);
-  const float sx = s32 * xmul, rx = __fdiv_rn(1.0f, sx);
+  XDomain xd;
+  const bool two_term = choose_domain(s32, xd);     // its barrier publishes the scale table too
   const int64_t steps = k / kStepK;
   const int64_t sgroups = (steps + kDecSteps - 1) / kDecSteps;
   const int64_t items = ((rows + kDecRows - 1) / kDecRows) * sgroups;
@@ -127,7 +126,6 @@ __global__ __launch_bounds__(256) void quantize_decode_kernel(
       for (int q = 0; q < 4; ++q) in.v[q] = make_uint4(0u, 0u, 0u, 0u);
     }
   };
-  __syncthreads();                                  // the scale table
   In cur;
   int64_t it = blockIdx.x;
   load(cur, it);
@@ -139,11 +137,9 @@ __global__ __launch_bounds__(256) void quantize_decode_kernel(
       uint32_t sb0 = 0u, sb1 = 0u;
       if (cur.ok) {
         float xs[16];
-        if (direct) to_fp8_domain<false>(cur.v[0], cur.v[1], 1.0f, sx, rx, xs);
-        else to_fp8_domain<true>(cur.v[0], cur.v[1], xmul, sx, rx, xs);
+        to_x_uniform(two_term, xd, cur.v[0], cur.v[1], xs);
         quantize_xs<kMode, false>(xs, tab, c0, sb0, make_uint4(0, 0, 0, 0));
-        if (direct) to_fp8_domain<false>(cur.v[2], cur.v[3], 1.0f, sx, rx, xs);
-        else to_fp8_domain<true>(cur.v[2], cur.v[3], xmul, sx, rx, xs);
+        to_x_uniform(two_term, xd, cur.v[2], cur.v[3], xs);
         quantize_xs<kMode, false>(xs, tab, c1, sb1, make_uint4(0, 0, 0, 0));
         const int64_t row = (it / sgroups) * kDecRows + rl;
         const int64_t st = (it % sgroups) * kDecSteps + j;

@@ -135,6 +135,44 @@ __device__ __forceinline__ void to_fp8_domain_two_term(uint4 v0, uint4 v1, float
   }
 }
 
+// The FP8 domain x = fl32(X / s32): from the two-term reciprocal {rh, rl} of
+// s32 where the check below allows it, otherwise X * xmul (exact) divided by
+// sx = s32 * xmul with Markstein's step on rx = fl32(1 / sx).
+struct XDomain {
+  float xmul, sx, rx, rh, rl;
+};
+
+// Fills xd for tensor scale s32 and tells whether the two-term division may
+// be used: s32 in [2^-90, 2^120] and every one of the 128 bf16 mantissas
+// divided this way gives Markstein's (exact) quotient.  The workgroup's first
+// 128 threads check; every thread calls it, and it holds a barrier.
+__device__ __forceinline__ bool choose_domain(float s32, XDomain& xd) {
+  const bool direct = s32 >= 0x1p-90f && s32 <= 0x1p120f;
+  xd.xmul = direct ? 1.0f : (s32 < 1.0f ? 0x1p64f : 0x1p-64f);
+  xd.sx = s32 * xd.xmul;
+  xd.rx = __fdiv_rn(1.0f, xd.sx);
+  const ScaleRecip r32 = scale_recip(s32);
+  xd.rh = r32.rh;
+  xd.rl = r32.rl;
+  int ok = 1;
+  if (direct && threadIdx.x < 128) {
+    // mantissa t at the exponent of s32, so that the quotient is near 1
+    const float xt = __uint_as_float((__float_as_uint(s32) & 0x7F800000u) | (threadIdx.x << 16));
+    ok = __float_as_uint(div_rn(xt, xd.sx, xd.rx)) == __float_as_uint(div_scale(xt, xd.rh, xd.rl));
+  }
+  return __syncthreads_and(ok) && direct;
+}
+
+// x of one block, by a uniform branch (two multiplies and fmas an element
+// against four with Markstein's step).
+__device__ __forceinline__ void to_x_uniform(bool two_term, const XDomain& xd, uint4 v0, uint4 v1,
+                                             float (&xs)[16]) {
+  if (two_term)
+    to_fp8_domain_two_term(v0, v1, xd.rh, xd.rl, xs);
+  else
+    to_fp8_domain<true>(v0, v1, xd.xmul, xd.sx, xd.rx, xs);
+}
+
 // Elements J, J+1 (J even) of a block, E2M1 branch: y = fl32(x / s_F)
 // rounded by the gfx950 FP4 converter (scale 1: nearest, ties to the even
 // code, saturating at 6, sign kept) into nibble pair (J%8)/2 of pf[J/8].

@@ -155,14 +155,6 @@ __global__ void finalize_scale(uint32_t* p) {
   *reinterpret_cast<float*>(p) = tensor_scale_of(*p >> 16);
 }
 
-// The FP8 domain x = fl32(X / s32): kTwoTerm from the two-term reciprocal
-// {rh, rl} of s32 (tensor scales that passed the check below), otherwise
-// X * xmul (exact) divided by sx = s32 * xmul with Markstein's step on
-// rx = fl32(1 / sx).
-struct XDomain {
-  float xmul, sx, rx, rh, rl;
-};
-
 // How x = fl32(X / s32) is computed: the two-term reciprocal of s32
 // (kTwoTerm), Markstein's step on X (kMarkstein), or Markstein's step on
 // X * xmul for tensor scales outside [2^-90, 2^120] (kScaledX).
@@ -354,19 +346,7 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(
   const float s32 = load_tensor_scale(tensor_scale);
   const bool direct = s32 >= 0x1p-90f && s32 <= 0x1p120f;
   XDomain xd;
-  xd.xmul = direct ? 1.0f : (s32 < 1.0f ? 0x1p64f : 0x1p-64f);
-  xd.sx = s32 * xd.xmul;
-  xd.rx = __fdiv_rn(1.0f, xd.sx);
-  const ScaleRecip r32 = scale_recip(s32);
-  xd.rh = r32.rh;
-  xd.rl = r32.rl;
-  int ok = 1;
-  if (direct && threadIdx.x < 128) {
-    // mantissa t at the exponent of s32, so that the quotient is near 1
-    const float xt = __uint_as_float((__float_as_uint(s32) & 0x7F800000u) | (threadIdx.x << 16));
-    ok = __float_as_uint(div_rn(xt, xd.sx, xd.rx)) == __float_as_uint(div_scale(xt, xd.rh, xd.rl));
-  }
-  const bool two_term = __syncthreads_and(ok) && direct;
+  const bool two_term = choose_domain(s32, xd);     // its barrier publishes the scale table too
   if constexpr (kContig && !kHad) {
     __shared__ __attribute__((aligned(1024))) uint8_t ring[(kThreads / 64) * 2 * kWindowBytes];
     if (two_term)
@@ -392,19 +372,19 @@ __global__ __launch_bounds__(kThreads) void quantize_kernel(
 // elements): one launch, at most one block per thread.  Every workgroup reads
 // the whole tensor for max|X| (a few hundred KB, from L2 after the first), so
 // all of them hold the same s32 without talking to each other; workgroup 0
-// stores it.  The read walks blocks in the order of the quantize assignment
-// (block w * kT + t of workgroup w of kT threads goes to its thread t), so
-// each thread keeps its own block from that pass and quantizes it without a
-// second read.  The maximum is order-independent: the result is the
+// stores it.  Workgroup w quantizes blocks [256 w, 256 w + 256), by the 256
+// threads that met them in the read (block r kT + t is read by thread t in
+// turn r), which kept them: no second read, and one wave of arithmetic per
+// SIMD however many threads read.  The maximum is order-independent: the result is the
 // two-pass one, bit for bit.
 //
-// Latency-bound: one chain of read, reduce, quantize.  Workgroups as small
-// as reads of eight blocks per thread allow spread the arithmetic over the
-// CUs (up to 2048 blocks, 256 threads: one wave per SIMD, where 1024 threads
-// ran four waves behind each other), and no more loads are in flight than
-// the tensor has blocks: always eight, a one-token call read its last block
-// seven times over.  1 x 4096: 5.1 -> 2.9 us, 3 x 4096 6.6 -> 3.2, 16 x 4096
-// 6.6 -> 4.8 (one launch included).  From 2^17 elements on the maximum pass of
+// Latency-bound: one chain of read, reduce, quantize.  Workgroups have as
+// many threads as keep a turn of eight blocks per thread, and no more loads
+// are in flight than the tensor has blocks: always eight, a one-token call
+// read its last block seven times over.  Quantizing 1024 blocks in a
+// workgroup ran four waves of the arithmetic behind each other.  1 x 4096:
+// 5.1 -> 2.9 us, 3 x 4096 6.6 -> 3.2, 16 x 4096 6.6 -> 4.7, 16 x 8192 6.7 -> 5.7
+// (one launch included).  From 2^17 elements on the maximum pass of
 // its own is faster (64 x 4096: 9.5 us here, 7.9 there).
 constexpr int64_t kSmallElems = int64_t(1) << 17;
 
@@ -422,7 +402,9 @@ __global__ __launch_bounds__(kT) void quantize_small_kernel(
   };
   // max|X| as bf16 magnitude bits
   const int64_t rounds = (nblocks + kT - 1) / kT;
-  const int64_t mine = blockIdx.x;                  // round holding this thread's block
+  constexpr int kGroups = kT / 256;                 // workgroups that share a turn's blocks
+  const int64_t turn = blockIdx.x / kGroups;        // the turn that reads this workgroup's blocks
+  const bool mine = (int)(threadIdx.x >> 8) == (int)(blockIdx.x % kGroups);
   uint32_t mx = 0u;
   uint4 k0 = make_uint4(0, 0, 0, 0), k1 = k0;
   for (int64_t r0 = 0; r0 < rounds; r0 += kFlight) {
@@ -439,7 +421,7 @@ __global__ __launch_bounds__(kT) void quantize_small_kernel(
 #pragma unroll
     for (int j = 0; j < kFlight; ++j) {
       mx = max(mx, max(absmax8(v0[j]), absmax8(v1[j])));
-      if (r0 + j == mine) {
+      if (r0 + j == turn) {
         k0 = v0[j];
         k1 = v1[j];
       }
@@ -454,8 +436,8 @@ __global__ __launch_bounds__(kT) void quantize_small_kernel(
   const float s32 = tensor_scale_of(r);
   if (blockIdx.x == 0 && threadIdx.x == 0) *tensor_scale = s32;
 
-  const int64_t g = mine * kT + threadIdx.x;
-  if (g >= nblocks) return;
+  const int64_t g = turn * kT + threadIdx.x;
+  if (!mine || g >= nblocks) return;
   const bool direct = s32 >= 0x1p-90f && s32 <= 0x1p120f;
   float xs[16];
   if (direct) {
@@ -646,7 +628,7 @@ template <int kMode, bool kSR, int kT, int kFlight>
 void launch_small_kernel(const uint16_t* x, int64_t nbk, int64_t ldx, int64_t nblocks, bool contig,
                          uint8_t* codes, uint8_t* scales, float* tensor_scale, const SrParams& sr,
                          hipStream_t stream) {
-  const int64_t g = (nblocks + kT - 1) / kT;   // one block per thread
+  const int64_t g = (nblocks + 255) / 256;     // 256 blocks per workgroup
   if (contig)
     quantize_small_kernel<true, kMode, kSR, kT, kFlight><<<(unsigned)g, kT, 0, stream>>>(
         x, nbk, ldx, nblocks, codes, scales, tensor_scale, sr);
