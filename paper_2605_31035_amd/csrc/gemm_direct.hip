@@ -22,18 +22,18 @@
 //
 // Loads.  All operands but the scales go straight from memory to LDS
 // (16-byte buffer loads): A in blocks of 32 K through a ring of ST stages
-// (one per share of K, its loads dealt over the NW waves), W in windows of
-// 128 K, 64 bytes per row and load, private to each wave.  Loaded by every
+// (one per share of K, its loads dealt over the NW waves), W in a ring of WR
+// windows of 128 K, 64 bytes per row and load, private to each wave.  Loaded by every
 // lane into registers instead, a W row's 16-byte pieces and 4-byte scale
 // words cost the texture unit a line each and held up the MFMAs: 128 x 11008
 // x 4096 on TM = 4, NW = 4 took 66 us with them and 60 us without.  Scales
 // come 16 bytes (256 K) at a time per row.
 //
 // Measured (with A's decode; before = the faster of the fused and two-pass
-// kernels): 32 x 14336 x 4096 44.8 -> 16.7 us, 64 x 14336 x 4096 45.7 ->
-// 21.4, 64 x 4096 x 11008 110.9 -> 21.5, 128 x 11008 x 4096 45.8 -> 25.3,
-// 256 x 4096 x 4096 45.2 -> 19.2, 509 x 11008 x 4096 74.8 -> 58.4,
-// 1024 x 4096 x 4096 50.4 -> 45.0, 2048 x 4096 x 4096 77 -> 73.  The decode
+// kernels): 32 x 14336 x 4096 44.8 -> 16.2 us, 64 x 14336 x 4096 45.7 ->
+// 19.2, 64 x 4096 x 11008 110.9 -> 20.1, 128 x 11008 x 4096 45.8 -> 25.3,
+// 256 x 4096 x 4096 45.2 -> 19, 509 x 11008 x 4096 74.8 -> 56.5, 1024 x 4096
+// x 4096 50.4 -> 45.  The decode
 // costs nothing beside the MFMAs from TM = 4 on; the MFMAs alone (no loads,
 // no decode) take 44 of the 60 us of a lone 128 x 256 tile at K = 4096.
 #include <type_traits>
@@ -68,7 +68,6 @@ __device__ __forceinline__ i32x4 raw_range(const void* base, uint32_t bytes) {
 }
 
 constexpr int kStepK64 = 64;       // K step of the main loop: four 16-K slices
-constexpr int kWinRing = 3;
 
 // Four dwords at a 4-byte aligned address.
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -92,7 +91,7 @@ __device__ __forceinline__ void slice_order() {
   }
 }
 
-template <int TM, int TN, int KW, int NW, int ST, int MINB>
+template <int TM, int TN, int KW, int NW, int ST, int WR, int MINB>
 __global__ __launch_bounds__(64 * KW * NW, MINB) void gemm_direct_kernel(
     const uint8_t* __restrict__ ablk, const uint8_t* __restrict__ w_codes,
     const uint8_t* __restrict__ w_scales, const float* __restrict__ a_ts,
@@ -106,11 +105,14 @@ __global__ __launch_bounds__(64 * KW * NW, MINB) void gemm_direct_kernel(
   constexpr int kUnits = TM * TN * 4;                // accumulator quads of a wave
   static_assert(L * NW == 2 * TM, "the waves share a stage's loads evenly");
   constexpr int kRingA = ST * kBlkA;
-  constexpr int kRingW = kWinRing * kWinBytes;
+  constexpr int kRingW = WR * kWinBytes;
   constexpr int kRedBytes = KW == 1 ? 0 : KW == 2 ? NW * kUnits * 1024 : KW * NW * kUnits * 1024;
   constexpr int kRings = KW * kRingA + KW * NW * kRingW;
   constexpr int kLds = kRings > kRedBytes ? kRings : kRedBytes;
-  static_assert(ST >= 3 && ST <= 8, "a W window must have landed when its first step is read");
+  // a W window must have landed when its first step is read: with WR = 3
+  // it is issued 8 blocks before, with WR = 2 4, and read after the wait of
+  // the sixth (second) block after it
+  static_assert(ST >= 3 && (WR == 3 ? ST <= 8 : WR == 2 && ST <= 4), "window distance");
   __shared__ __attribute__((aligned(1024))) uint8_t lds[kLds];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -257,8 +259,8 @@ __global__ __launch_bounds__(64 * KW * NW, MINB) void gemm_direct_kernel(
     u32x4a4 sn[TN];
     uint32_t sc[TN][4];
     load_s(sn, 0);
-    issue_w(0, 0);
-    issue_w(kWinBytes, 1);
+#pragma unroll
+    for (int v = 0; v < WR - 1; ++v) issue_w(v * kWinBytes, v);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int s = 0; s < ST - 1; ++s)
@@ -277,14 +279,14 @@ __global__ __launch_bounds__(64 * KW * NW, MINB) void gemm_direct_kernel(
     read_a(pa, 0, 0);
     decode_w(pb, cur, sc, 0, 0);
     int rd = 0, wr = (ST - 1) * kBlkA;               // slots of block s and of block s + ST - 1
-    int wcur = 0, wfill = 2 * kWinBytes;              // slots of this W window and of the one two ahead
+    int wcur = 0, wfill = (WR - 1) * kWinBytes;       // slots of this W window and of the one WR - 1 ahead
     // One 64-K step u (step j of four whose scales are in sc): two blocks of
     // 32 K, each two slices.  Slice by slice, the next slice's A fragments
     // are read and its W fragments decoded while this slice's MFMAs run.
     auto step = [&](auto J_, int u) {
       constexpr int j = decltype(J_)::value;
       if constexpr (j == 0) load_s(sn, u + 4);
-      if constexpr (j % 2 == 0) issue_w(wfill, u / 2 + 2);
+      if constexpr (j % 2 == 0) issue_w(wfill, u / 2 + WR - 1);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
@@ -425,36 +427,41 @@ __global__ __launch_bounds__(64 * KW * NW, MINB) void gemm_direct_kernel(
   }
 }
 
-template <int TM, int TN, int KW, int NW, int ST, int MINB>
+template <int TM, int TN, int KW, int NW, int ST, int WR, int MINB>
 hipError_t launch(const uint8_t* ablk, const float* a_ts, const uint8_t* w_codes,
                   const uint8_t* w_scales, const float* w_ts, int64_t m, int64_t n, int64_t k,
                   float* c, hipStream_t stream) {
   const int64_t tiles = ((m + 32 * TM - 1) / (32 * TM)) * ((n + 32 * TN * NW - 1) / (32 * TN * NW));
-  gemm_direct_kernel<TM, TN, KW, NW, ST, MINB><<<(unsigned)tiles, 64 * KW * NW, 0, stream>>>(
+  gemm_direct_kernel<TM, TN, KW, NW, ST, WR, MINB><<<(unsigned)tiles, 64 * KW * NW, 0, stream>>>(
       ablk, w_codes, w_scales, a_ts, w_ts, m, n, k, c, n);
   return hipGetLastError();
 }
 
 // The tile configurations, with what one round of workgroups (`per_cu` on
-// every CU) costs: `fixed` us and `per_k` us for every 4096 of K, or `low` in
-// a round that leaves a third of the CUs idle (per_cu = 1), or gives each
-// only one workgroup of two.  From full and partial rounds: 128, 256 and 512
-// workgroups of the first seven take 8.3, 8.5, 18.2 | 11.8, 15.5, 30.1 | 9.5,
-// 10.4, 22.7 | 14.9, 19.8, 38.4 | 27.2, 32.2, 61.5 | 21.4, 24.7, 48.4 | 38.9,
-// 43.6, 85.8 us at K = 4096 (one launch included); 172 and 256 of the eighth
-// 55 and 67 us; 256, 258 and 344 of the last 68.7, 97 and 102, and 109 a
-// round over eight rounds.
+// every CU) costs, one launch included: `fixed` us and `per_k` us for every
+// 4096 of K, or `low` in a round that leaves a third of the CUs idle (per_cu
+// = 1) or gives each only one workgroup of two.  Measured at K = 4096 with
+// 128, 256, 344 and 512 workgroups (two rows of tiles from 256 on), us:
+//   32 x 32    7.6   7.8  14.0  14.3     64 x 128  27.4  29.6  51.6   57.0
+//   32 x 64   11.2  11.9  22.6  25.2    128 x 64   20.9  24.5  42.7   48.5
+//   64 x 32    9.3  10.8  19.1  20.8    128 x 128  39.1  41.5  58.7   69.7
+//   64 x 64   13.1  16.2  28.7  33.1    128 x 256  54.4  67.4 113.1  132.0
+//   128 x 256, two on a CU: 64.0 75.0 104.6 126.8 (97 with 258, and 109 a
+//   round over eight rounds of a 16384 x 8192 x 8192 product)
+// The first three and the fourth split K over eight waves: 64 x 14336 x 4096
+// on 64 x 64 tiles takes 16.3 us with eight waves and two W windows, 18.6
+// with four waves and three.
 struct DirectTile {
   int rows, cols, per_cu;
   int k_multiple;          // shares of K must be equal where waves step together
   float fixed, per_k, low;
 };
 constexpr DirectTile kTiles[] = {
-    {32, 32, 1, 64, 1.2f, 7.0f, 6.5f},         {32, 64, 1, 64, 1.5f, 13.0f, 10.5f},
-    {64, 32, 1, 64, 1.5f, 9.0f, 7.5f},         {64, 64, 1, 64, 1.5f, 17.0f, 14.0f},
-    {64, 128, 1, 64 * 4, 1.5f, 29.0f, 25.0f},  {128, 64, 1, 64, 1.5f, 22.0f, 19.5f},
-    {128, 128, 1, 64 * 2, 1.5f, 40.0f, 36.0f}, {128, 256, 1, 64 * 2, 5.0f, 60.0f, 49.0f},
-    {128, 256, 2, 64, 6.0f, 107.0f, 61.0f},
+    {32, 32, 2, 64, 0.5f, 13.8f, 7.2f},        {32, 64, 1, 64, 1.3f, 11.5f, 10.0f},
+    {64, 32, 1, 64, 2.0f, 8.5f, 7.3f},         {64, 64, 1, 64, 1.5f, 15.0f, 11.8f},
+    {64, 128, 1, 64 * 4, 1.5f, 28.0f, 26.0f},  {128, 64, 1, 64, 1.5f, 22.5f, 19.5f},
+    {128, 128, 2, 64 * 2, 3.0f, 66.5f, 37.0f}, {128, 256, 1, 64 * 2, 5.0f, 61.0f, 48.5f},
+    {128, 256, 2, 64, 6.0f, 108.0f, 61.0f},
 };
 constexpr int kTileCount = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
 
@@ -465,7 +472,7 @@ float tile_cost(const DirectTile& t, int64_t m, int64_t n, int64_t k, int64_t cu
   float us = (float)full * (t.fixed + t.per_k * kf);
   const float kk = kf * t.per_k;
   if (rest > cus)                 // two workgroups on some CUs
-    us += t.fixed + kk * (0.86f + 0.14f * (float)(rest - cus) / (float)cus);
+    us += t.fixed + kk * (0.83f + 0.17f * (float)(rest - cus) / (float)cus);
   else if (rest > 0)
     us += t.fixed + (t.per_cu == 2 || 3 * rest <= 2 * cus + 16 ? t.low * kf : kk);
   return us;
@@ -499,15 +506,15 @@ hipError_t launch_gemm_direct(int tile, const uint8_t* ablk, const float* a_ts,
   if (tile < 0 || tile >= kTileCount || k < 256 || k % kTiles[tile].k_multiple != 0)
     return hipErrorInvalidValue;
   switch (tile) {
-    case 0: return launch<1, 1, 8, 1, 6, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
-    case 1: return launch<1, 2, 8, 1, 3, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
-    case 2: return launch<2, 1, 8, 1, 3, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
-    case 3: return launch<2, 2, 4, 1, 3, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
-    case 4: return launch<2, 2, 4, 2, 3, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
-    case 5: return launch<4, 2, 4, 1, 3, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
-    case 6: return launch<4, 2, 2, 2, 3, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
-    case 7: return launch<4, 2, 2, 4, 3, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
-    default: return launch<4, 2, 1, 4, 4, 2>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
+    case 0: return launch<1, 1, 8, 1, 4, 2, 2>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
+    case 1: return launch<1, 2, 8, 1, 4, 2, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
+    case 2: return launch<2, 1, 8, 1, 4, 2, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
+    case 3: return launch<2, 2, 8, 1, 3, 2, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
+    case 4: return launch<2, 2, 4, 2, 3, 3, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
+    case 5: return launch<4, 2, 4, 1, 3, 3, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
+    case 6: return launch<4, 2, 2, 2, 3, 2, 2>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
+    case 7: return launch<4, 2, 2, 4, 4, 2, 1>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
+    default: return launch<4, 2, 1, 4, 4, 3, 2>(ablk, a_ts, w_codes, w_scales, w_ts, m, n, k, c, stream);
   }
 }
 

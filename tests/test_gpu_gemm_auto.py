@@ -47,13 +47,13 @@ def _need(m, n, k):
 # with ragged edges, every K remainder of 256 and shares of K that are empty
 # (256) or differ by a step.
 @pytest.mark.parametrize("m,n,k", [
-    (17, 33, 256), (64, 4090, 576), (33, 130, 320),        # 32 x 32
-    (31, 8200, 320), (17, 17003, 576),                     # 32 x 64
-    (257, 1000, 384), (128, 4090, 256),                    # 64 x 32
-    (33, 9001, 320), (64, 8200, 1024),                     # 64 x 64
-    (129, 17003, 256), (31, 17003, 1024),                  # 64 x 128
-    (65, 8200, 576), (509, 11008, 320),                    # 128 x 64
-    (33, 17003, 384), (509, 17003, 256),                   # 128 x 128
+    (17, 33, 256), (64, 4090, 576), (33, 130, 320), (31, 8200, 320), (129, 17003, 320),   # 32 x 32
+    (31, 14300, 3008), (17, 16300, 4096),                  # 32 x 64
+    (100, 4090, 4096), (128, 4090, 3008),                  # 64 x 32
+    (33, 9001, 320), (64, 8200, 1024), (64, 28672, 576),   # 64 x 64
+    (129, 17003, 256), (33, 17003, 1024),                  # 64 x 128
+    (65, 8200, 576), (509, 11001, 320),                    # 128 x 64
+    (65, 17003, 384), (509, 16300, 256),                   # 128 x 128
     (500, 11001, 1024),                                    # 128 x 256, K halved over the waves
     (129, 28672, 320), (509, 28672, 576),                  # 128 x 256, two workgroups per CU
 ])
@@ -61,7 +61,7 @@ def test_direct_tiles(m, n, k):
     import paper_2605_31035_amd as M
     log(f"direct gemm m={m} n={n} k={k}")
     assert _need(m, n, k) == (m + 255) // 256 * 256 * k * 2     # A decoded, W packed
-    if m * k < 1 << 20:
+    if n * k < 1 << 22:
         qa, qw = Q.quantize(W.adversarial(m + 3 * k, m, k)), Q.quantize(W.adversarial(n + k, n, k))
         a, w = _dev(qa), _dev(qw)
     else:                                                       # quantized on the device
