@@ -88,8 +88,16 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
 // contiguous memory, with the non-temporal hint (X is read once here), the
 // next window's loads in flight while this one is reduced.  Windows past the
 // end read zeros (buffer range check), which leave the maximum unchanged.
+// X of 32 to 160 MB is loaded without the hint, so that the quantize pass
+// finds it in the 256 MB infinity cache: a 2D weight of 11008 x 4096 62.3 ->
+// 57.9 us in a loop over three of them (its second pass 45 -> 39 us), 4096 x
+// 11008 45.9 -> 45.4.  Smaller ones stay there anyway, and the pass itself is
+// faster with the hint (1537 x 4096: 14.4 against 14.8 us).
+constexpr int kNonTemporal = 2;
+constexpr int64_t kKeptFrom = int64_t(32) << 20, kKeptTo = int64_t(160) << 20;
 constexpr int kAmaxWindow = 256;      // vectors of 8 bf16 per wave per iteration
 
+template <int kAux>
 __global__ __launch_bounds__(kThreads) void amax_stream_kernel(const uint16_t* __restrict__ x,
                                                                 int64_t nvec,
                                                                 uint32_t* __restrict__ partials,
@@ -108,7 +116,7 @@ __global__ __launch_bounds__(kThreads) void amax_stream_kernel(const uint16_t* _
         const_cast<uint16_t*>(x + base * 8), 0, (int)(rem * 16), 0x00020000);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-      v[j] = __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + j * 1024, 0, 2);
+      v[j] = __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16 + j * 1024, 0, kAux);
   };
   u32x4 cur[4], nxt[4];
   load(0, cur);
@@ -582,12 +590,16 @@ hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k, int64
     // workgroups per CU (a persistent grid for large tensors)
     static ResidentCache cache;
     const int64_t wanted = (total + 4 * kAmaxWindow - 1) / (4 * kAmaxWindow);
-    const int64_t resident = resident_groups(amax_stream_kernel, cache, 4);
+    const int64_t resident = resident_groups(amax_stream_kernel<kNonTemporal>, cache, 4);
     const int g = (int)(wanted < resident ? (wanted > 0 ? wanted : 1) : resident);
     return tensor_scale_with(total, g, scratch, scratch_bytes, tensor_scale, stream, own, in,
                              [&](int grid, uint32_t* partials, uint32_t* out) {
-                               amax_stream_kernel<<<grid, kThreads, 0, stream>>>(x, total,
-                                                                                  partials, out);
+                               if (total * 16 >= kKeptFrom && total * 16 <= kKeptTo)
+                                 amax_stream_kernel<0><<<grid, kThreads, 0, stream>>>(
+                                     x, total, partials, out);
+                               else
+                                 amax_stream_kernel<kNonTemporal><<<grid, kThreads, 0, stream>>>(
+                                     x, total, partials, out);
                              });
   }
   // up to 1024 workgroups x 256 threads x 4 loads of 16 B keeps ~16 MB in flight
