@@ -374,7 +374,7 @@ __device__ __forceinline__ uint2 sr_codes_ties(const float (&xs)[16], const Scal
 // largest magnitude is the code's.  A sum with zero fraction bits may be a
 // tie (or hide bits that trunc dropped): the few lanes that see one redo the
 // block.  `sign`: bit 3 of every nibble of a negative X.  About 15
-// instructions per element against 30; 2^28 elements, s32 given: 334 -> 242 us.
+// instructions per element against 30; 2^28 elements, s32 given: 334 -> 232 us.
 __device__ __forceinline__ uint2 sr_codes(const float (&xs)[16], const ScaleRecip& sc, bool int4,
                                           uint4 rnd, uint2 sign) {
   const float up = int4 ? 0x1p22f : 0x1p23f;

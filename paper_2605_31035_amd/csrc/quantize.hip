@@ -677,9 +677,13 @@ hipError_t launch_mode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, 
   if (ldx == k && !kHad) {
     // Contiguous X (stream_loop): one window of 64 blocks per wave, four
     // per workgroup; a tensor with more windows is walked by a persistent
-    // grid of at most 3 workgroups per CU (measured on the 2^28 tensor: 3,
-    // 4 and 6 per CU within 3% for every mode, 3 the fastest or tied).
-    constexpr int kStreamPerCU = 3;
+    // grid of at most 4 workgroups per CU.  Against 3 per CU, with the scale
+    // computed: 1537 x 4096 14.4 -> 13.5 us, 4096 x 4096 22.8 -> 21.1, 8192 x
+    // 8192 63 -> 60; s32 given, 2^28 elements 145 -> 141, with stochastic
+    // rounding 242 -> 232 (6 per CU: 17 us on 1537 x 4096).  The single-format
+    // encodings do little arithmetic per byte and stream better with 3 (E2M1
+    // on 2^28 elements 110 us against 115).
+    constexpr int kStreamPerCU = !kSR && (kMode == kForceE2M1 || kMode == kForceE1M2) ? 3 : 4;
     const int64_t wanted = (nblocks + kThreads - 1) / kThreads;
     const int64_t capped =
         resident_groups(quantize_kernel<true, kMode, kSR, kHad>, capped_c, kStreamPerCU);
