@@ -328,7 +328,7 @@ int mixfp4_gemm_ws(const uint8_t *a_codes, const uint8_t *a_scales,
 /*
  * mixfp4_gemm_auto - mixfp4_gemm with caller-supplied device workspace, on
  * the route expected to be the fastest for the shape: without workspace
- * (decode shapes, K % 32 != 0 and small products of K % 64 != 0), with A
+ * (decode shapes, K % 32 != 0 and small products of K < 512), with A
  * decoded once into the workspace and W decoded on its way into the matrix
  * instructions (m > 16 up to about a thousand rows, K % 64 == 0, K >= 256), or
  * the two passes of mixfp4_gemm_ws.  The routes differ only in the order of

@@ -438,13 +438,17 @@ float two_pass_us(int64_t m, int64_t n, int64_t k) {
 // The direct one has to be 8% cheaper: its decode beside the MFMAs draws
 // power that lowers the clock, most in a longer run of GEMMs (2048 x 4096 x
 // 11008 alone: 173 against 178 us, but inside a layer's backward pass the
-// whole pass took 553 us with it and 544 without).  Other K: two passes from
-// m n / (m + n) = 1280 on, as measured against the fused kernel.
+// whole pass took 553 us with it and 544 without).  K % 64 = 32: the fused
+// kernel's masked loads lose to two passes from 17 rows on (17 x 11008 x
+// 4000 79 against 69 us, 512 x 11008 x 4000 220 against 79, 17 x 2048 x 1056
+// 23 against 22); below K = 512, where the launches count, and for K < 256,
+// two passes from m n / (m + n) = 1280 on.
 GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k) {
   if (!gemm_two_pass_applies(m, n, k)) return {GemmRoute::kNoWorkspace, 0, 0};
   const int64_t both = gemm_two_pass_workspace(m, n, k);
   if (!gemm_direct_applies(m, n, k))
-    return m * n >= 1280 * (m + n) ? GemmPlan{GemmRoute::kTwoPass, 0, both}
+    return (k % 64 != 0 && k >= 512) || m * n >= 1280 * (m + n)
+               ? GemmPlan{GemmRoute::kTwoPass, 0, both}
                                    : GemmPlan{GemmRoute::kNoWorkspace, 0, 0};
   float us = 0.0f;
   const int tile = gemm_direct_tile(m, n, k, &us);

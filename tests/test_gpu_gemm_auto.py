@@ -103,3 +103,16 @@ def test_direct_falls_back():
     odd.copy_(w[1].reshape(-1))
     assert odd.data_ptr() % 4 == 1
     _check(host(call(odd, need)), qa, qw, m, n)
+
+
+@pytest.mark.parametrize("m,n,k", [(17, 33, 544), (70, 300, 1056)])
+def test_k_of_32_takes_two_passes(m, n, k):
+    """K % 64 = 32 from 512 on: both operands decoded, bit for bit as with the
+    workspace given."""
+    import paper_2605_31035_amd as M
+    assert _need(m, n, k) == M.mixfp4_gemm_workspace_size(m, n, k) > 0
+    qa, qw = Q.quantize(W.adversarial(m, m, k)), Q.quantize(W.adversarial(n, n, k))
+    a, w = _dev(qa), _dev(qw)
+    c = M.mixfp4_gemm(a, w, workspace="auto")
+    assert torch.equal(c, M.mixfp4_gemm(a, w, workspace=True))
+    _check(host(c), qa, qw, m, n)
