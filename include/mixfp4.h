@@ -148,7 +148,9 @@ int mixfp4_quantize_ex(const uint16_t *x, int64_t rows, int64_t k, int64_t ldx,
  * mixfp4_quantize_decode with caller-owned device scratch for the tensor-scale pass: with at least
  * mixfp4_quantize_scratch_bytes() (4096) bytes, 4-byte aligned, the
  * per-workgroup maxima are kept there and folded by the quantize kernel,
- * which saves a launch.  Outputs are the same, bit for bit.  The scratch's
+ * which saves a launch.  A quantization rotated by 128 or 256 that computes its
+ * scale (not transposed), with 2 * rows * k bytes more than that, 16-byte aligned, keeps
+ * the rotated tensor there instead of rotating X twice.  Outputs are the same, bit for bit.  The scratch's
  * contents on entry are ignored and on return unspecified; it must not be
  * used by anything else until the call's work is done (same stream is
  * enough).  scratch == NULL or less of it: as the function without _ws;

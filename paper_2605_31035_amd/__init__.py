@@ -159,7 +159,8 @@ def mixfp4_quantize(x: torch.Tensor, tensor_scale: torch.Tensor | None = None,
         flags |= TRANSPOSE
     signs = _signs_arg(hadamard_signs, hadamard_block) if flags & (STOCHASTIC | TRANSPOSE) \
         or hadamard_block else None
-    _keep, scr, scr_bytes = _scratch(rows * k if tensor_scale is None else 0, dev)
+    _keep, scr, scr_bytes = _scratch(rows * k if tensor_scale is None else 0, dev,
+                                     hadamard_block >= 128 and not transpose)
     st = lib.mixfp4_quantize_ws(_ptr(x), rows, k, ldx, _ptr(codes), _ptr(scales), _ptr(ts),
                                 flags, hadamard_block, _ptr(signs),
                                 seed & 0xFFFFFFFFFFFFFFFF, offset & 0xFFFFFFFFFFFFFFFF,
@@ -173,15 +174,28 @@ mixfp4_quantize_ex = mixfp4_quantize
 _SCRATCH_WORDS = lib.mixfp4_quantize_scratch_bytes() // 4
 
 
-def _scratch(elements: int, dev):
+_ROTATED_ELEMS = 1 << 26   # largest tensor whose rotated copy is taken as scratch
+
+
+def _scratch(elements: int, dev, rotated: bool = False):
     """(tensor to keep, pointer, bytes) of the scratch of a tensor-scale pass
-    over so many elements (none where that pass is not a launch of its own).
+    over so many elements (none where that pass is not a launch of its own),
+    with room for the rotated tensor if that memory is there.
     The caching allocator may hand it out again once this call returns, which
     the stream orders behind the launches."""
     if elements <= 1 << 17:
         return None, None, 0
-    t = torch.empty(_SCRATCH_WORDS, dtype=torch.int32, device=dev)
-    return t, _ptr(t), 4 * _SCRATCH_WORDS
+    words = _SCRATCH_WORDS
+    if rotated and elements <= _ROTATED_ELEMS:
+        try:
+            words += elements // 2
+            t = torch.empty(words, dtype=torch.int32, device=dev)
+        except torch.OutOfMemoryError:
+            words = _SCRATCH_WORDS
+            t = torch.empty(words, dtype=torch.int32, device=dev)
+    else:
+        t = torch.empty(words, dtype=torch.int32, device=dev)
+    return t, _ptr(t), 4 * words
 
 
 def _signs_arg(signs, block):

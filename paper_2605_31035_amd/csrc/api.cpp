@@ -38,6 +38,16 @@ uint32_t* own_partials(void* scratch, int64_t bytes) {
              ? static_cast<uint32_t*>(scratch) : nullptr;
 }
 
+// Room for the rotated tensor behind the maxima of the caller's scratch, or
+// NULL: from Hadamard blocks of 128 on, where storing it beats a second
+// rotation (figures at amax_rotated_kernel).
+uint16_t* own_rotated(void* scratch, int64_t bytes, int64_t rows, int64_t k, int32_t block) {
+  const int64_t head = (int64_t)sizeof(uint32_t) * mixfp4::kScalePartials;
+  if (block < 128 || !scratch || bytes < head || !aligned(scratch, 16) || (bytes - head) / 2 / k < rows)
+    return nullptr;
+  return reinterpret_cast<uint16_t*>(static_cast<uint8_t*>(scratch) + head);
+}
+
 bool valid_hadamard_block(int32_t b) {
   return b == 16 || b == 32 || b == 64 || b == 128 || b == 256;
 }
@@ -100,15 +110,22 @@ int quantize_impl(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8
                                                        tensor_scale, opt, s));
   if (!given) {
     const int64_t nscr = empty ? 0 : rows * (k / mixfp4::kBlock);
+    uint16_t* y = opt.had && !empty
+                      ? own_rotated(scratch, scratch_bytes, rows, k, hadamard_block) : nullptr;
     const hipError_t e =
         opt.had ? mixfp4::launch_tensor_scale_rotated(x, empty ? 0 : rows, k, ldx, opt.hp,
                                                       empty ? nullptr : scales, nscr,
-                                                      tensor_scale, s, own, &in)
+                                                      tensor_scale, s, own, &in, y)
                 : mixfp4::launch_tensor_scale(x, empty ? 0 : rows, k, ldx,
                                               empty ? nullptr : scales, nscr, tensor_scale, s,
                                               own, &in);
     const int st = launch_status(e);
     if (st != MIXFP4_OK) return st;
+    if (y) {
+      x = y;
+      ldx = k;
+      opt.had = false;
+    }
   }
   if (empty) return MIXFP4_OK;
   return launch_status(mixfp4::launch_quantize(x, rows, k, ldx, codes, scales, in, opt, s));

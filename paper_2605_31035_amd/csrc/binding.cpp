@@ -123,6 +123,11 @@ PyObject* guarded(Body body) {
   Py_RETURN_NONE;
 }
 
+// Largest tensor whose rotated copy (2 bytes an element) is taken as scratch:
+// 128 MB, so that the extra memory of a call stays bounded (the copy pays for
+// any size).
+constexpr int64_t kRotatedElems = int64_t(1) << 26;
+
 // quantize(x, tensor_scale, flags, hadamard_block, signs, seed, offset)
 PyObject* quantize(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (n != 7) Py_RETURN_NONE;
@@ -160,8 +165,9 @@ PyObject* quantize(PyObject*, PyObject* const* args, Py_ssize_t n) {
     at::Tensor ts, scratch;
     if (!given) {
       ts = empty({1}, at::kFloat, *x);
+      const int64_t room = block >= 128 && !t && rows * k <= kRotatedElems ? 2 * rows * k : 0;
       if (rows * k > (int64_t(1) << 17))
-        scratch = empty({mixfp4_quantize_scratch_bytes()}, at::kByte, *x);
+        scratch = empty({mixfp4_quantize_scratch_bytes() + room}, at::kByte, *x);
     }
     const int st = mixfp4_quantize_ws(
         static_cast<const uint16_t*>(x->data_ptr()), rows, k, x->stride(0), bytes(codes),

@@ -105,12 +105,14 @@ hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k,
                                float* tensor_scale, hipStream_t stream,
                                uint32_t* partials = nullptr, ScaleIn* in = nullptr);
 // Tensor scale of the rotated tensor (the amax pass of a rotate-and-quantize
-// call); same contract as launch_tensor_scale.
+// call); same contract as launch_tensor_scale.  With y (rows * k values) the
+// rotated tensor is written there, contiguous.
 hipError_t launch_tensor_scale_rotated(const uint16_t* x, int64_t rows, int64_t k,
                                        int64_t ldx, const HadamardParams& hp,
                                        uint8_t* scratch, int64_t scratch_bytes,
                                        float* tensor_scale, hipStream_t stream,
-                                       uint32_t* partials = nullptr, ScaleIn* in = nullptr);
+                                       uint32_t* partials = nullptr, ScaleIn* in = nullptr,
+                                       uint16_t* y = nullptr);
 hipError_t launch_quantize(const uint16_t* x, int64_t rows, int64_t k,
                            int64_t ldx, uint8_t* codes, uint8_t* scales,
                            const ScaleIn& tensor_scale, const QuantOptions& opt,

@@ -466,10 +466,17 @@ __global__ __launch_bounds__(kT) void quantize_small_kernel(
 // rounded results), same lane-per-block walk as the quantizer so that every
 // Hadamard block sits in consecutive lanes of one wave.  Results go to
 // partials[blockIdx.x] or, without partials, into *out by atomic max.
-template <bool kContig>
+// kStore: the rotated tensor itself goes to y [rows, k] as well, for the
+// quantize kernel to read instead of rotating X a second time: bound by the
+// fp64 butterflies and conversions, so from b = 128 on the store is cheaper than
+// repeating them.  Whole call with the scale computed, b = 128, rotated twice
+// against stored: 1537 x 4096 20.7 -> 19.7 us, 4096 x 4096 42.3 -> 34.3, 8192 x
+// 8192 143 -> 106, 16384 x 16384 542 -> 388.  b = 16 exchanges nothing between
+// lanes and loses: 14.4 -> 16.8, 26.7 -> 26.7, 83.8 -> 86, 320 -> 347.
+template <bool kContig, bool kStore>
 __global__ __launch_bounds__(kThreads) void amax_rotated_kernel(
     const uint16_t* __restrict__ x, int64_t nbk, int64_t ldx, int64_t nblocks, HadamardParams hp,
-    uint32_t* __restrict__ partials, uint32_t* __restrict__ out) {
+    uint16_t* __restrict__ y, uint32_t* __restrict__ partials, uint32_t* __restrict__ out) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t g0 = rotated_index((int64_t)blockIdx.x * blockDim.x + threadIdx.x, hp);
   const SignMasks sm = load_sign_masks(hp, (int)g0 & ((1 << hp.lanes_log2) - 1));
@@ -482,9 +489,17 @@ __global__ __launch_bounds__(kThreads) void amax_rotated_kernel(
       const int64_t r = g / nbk;
       src = x + r * ldx + ((g - r * nbk) << 4);
     }
-    const uint4 v0 = *reinterpret_cast<const uint4*>(src);
-    const uint4 v1 = *reinterpret_cast<const uint4*>(src + 8);
-    m = max(m, hadamard_absmax(v0, v1, sm, hp));
+    uint4 v0 = *reinterpret_cast<const uint4*>(src);
+    uint4 v1 = *reinterpret_cast<const uint4*>(src + 8);
+    if (kStore) {
+      hadamard_rotate(v0, v1, sm, hp);
+      uint4* dst = reinterpret_cast<uint4*>(y + (g << 4));
+      dst[0] = v0;
+      dst[1] = v1;
+      m = max(m, max(absmax8(v0), absmax8(v1)));
+    } else {
+      m = max(m, hadamard_absmax(v0, v1, sm, hp));
+    }
   }
   for (int off = 32; off > 0; off >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
   __shared__ uint32_t wave_max[kThreads / 64];
@@ -612,26 +627,42 @@ hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k, int64
                            });
 }
 
-hipError_t launch_tensor_scale_rotated(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
-                                       const HadamardParams& hp, uint8_t* scratch,
-                                       int64_t scratch_bytes, float* tensor_scale,
-                                       hipStream_t stream, uint32_t* own, ScaleIn* in) {
+namespace {
+
+template <bool kStore>
+hipError_t tensor_scale_rotated(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
+                                const HadamardParams& hp, uint16_t* y, uint8_t* scratch,
+                                int64_t scratch_bytes, float* tensor_scale, hipStream_t stream,
+                                uint32_t* own, ScaleIn* in) {
   const int64_t nbk = k / kBlock, nblocks = rows * nbk;
   static ResidentCache cache_c, cache_s;
-  const int64_t resident = ldx == k ? resident_groups(amax_rotated_kernel<true>, cache_c)
-                                    : resident_groups(amax_rotated_kernel<false>, cache_s);
+  const int64_t resident = ldx == k ? resident_groups(amax_rotated_kernel<true, kStore>, cache_c)
+                                    : resident_groups(amax_rotated_kernel<false, kStore>, cache_s);
   const int64_t wanted = (nblocks + kThreads - 1) / kThreads;
   int g = (int)(wanted < resident ? wanted : resident);
   if (g < 1) g = 1;
   return tensor_scale_with(nblocks, g, scratch, scratch_bytes, tensor_scale, stream, own, in,
                            [&](int grid, uint32_t* partials, uint32_t* out) {
                              if (ldx == k)
-                               amax_rotated_kernel<true><<<grid, kThreads, 0, stream>>>(
-                                   x, nbk, ldx, nblocks, hp, partials, out);
+                               amax_rotated_kernel<true, kStore><<<grid, kThreads, 0, stream>>>(
+                                   x, nbk, ldx, nblocks, hp, y, partials, out);
                              else
-                               amax_rotated_kernel<false><<<grid, kThreads, 0, stream>>>(
-                                   x, nbk, ldx, nblocks, hp, partials, out);
+                               amax_rotated_kernel<false, kStore><<<grid, kThreads, 0, stream>>>(
+                                   x, nbk, ldx, nblocks, hp, y, partials, out);
                            });
+}
+
+}  // namespace
+
+hipError_t launch_tensor_scale_rotated(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
+                                       const HadamardParams& hp, uint8_t* scratch,
+                                       int64_t scratch_bytes, float* tensor_scale,
+                                       hipStream_t stream, uint32_t* own, ScaleIn* in,
+                                       uint16_t* y) {
+  return y ? tensor_scale_rotated<true>(x, rows, k, ldx, hp, y, scratch, scratch_bytes,
+                                        tensor_scale, stream, own, in)
+           : tensor_scale_rotated<false>(x, rows, k, ldx, hp, y, scratch, scratch_bytes,
+                                         tensor_scale, stream, own, in);
 }
 
 namespace {

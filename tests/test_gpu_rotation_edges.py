@@ -56,3 +56,23 @@ def test_scale_of_non_finite(b, transpose, bad):
     amax = torch.tensor([mag], dtype=torch.int32).to(torch.int16).view(torch.bfloat16).float()
     want = amax / 2688 if bool(amax > 0) else torch.ones(1)
     assert float(got) == float(want)
+
+
+@pytest.mark.parametrize("b,rows,k,pad,mode,rounding", [
+    (128, 1025, 128, 0, "mixfp4", "nearest"), (256, 515, 256, 16, "four_six", "nearest"),
+    (128, 347, 384, 16, "mixfp4", "stochastic"), (256, 257, 512, 0, "e2m1", "stochastic"),
+    (64, 300, 448, 0, "mixfp4", "nearest")])
+def test_rotated_copy_in_scratch(b, rows, k, pad, mode, rounding):
+    """The scratch with room for the rotated tensor (rows * k > 2^17), against
+    the same call on the rotated tensor and with the maxima's scratch only."""
+    import paper_2605_31035_amd as M
+    x = torch.from_numpy(W.adversarial(rows, rows, k + pad).view(np.int16)).cuda().view(
+        torch.bfloat16)[:, :k]
+    sg = torch.from_numpy(np.random.default_rng(b).choice([-1, 1], b).astype(np.int8)).cuda()
+    log(f"rotated copy b={b} {rows}x{k} pad={pad} {mode} {rounding}")
+    opt = dict(mode=mode, rounding=rounding, seed=5, offset=7)
+    got = M.mixfp4_quantize(x, hadamard_block=b, hadamard_signs=sg, **opt)
+    want = M.mixfp4_quantize(M.mixfp4_hadamard(x, b, sg), **opt)
+    twice = M.mixfp4_quantize(x, tensor_scale=got[2], hadamard_block=b, hadamard_signs=sg, **opt)
+    for g, w, t in zip(got, want, twice):
+        assert torch.equal(g, w) and torch.equal(g, t)
