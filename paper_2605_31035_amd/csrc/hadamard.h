@@ -117,8 +117,10 @@ __device__ __forceinline__ void hadamard_sums(uint4 v0, uint4 v1, const SignMask
   const int lane = (int)(threadIdx.x & 63u);
   if (hp.lanes_log2 >= 1) cross_stage<1>(v, lane);
   if (hp.lanes_log2 >= 2) cross_stage<2>(v, lane);
-  if (hp.lanes_log2 >= 3) cross_stage<8>(v, lane);
+  // ascending element bits, whatever L: beyond the exact span the result
+  // depends on the order of the stages
   if (hp.lanes_log2 >= 4) cross_stage<4>(v, lane);
+  if (hp.lanes_log2 >= 3) cross_stage<8>(v, lane);
 }
 
 // Rotate the lane's 16 bf16 values (v0: elements 0-7, v1: 8-15) in place.

@@ -76,3 +76,34 @@ def test_rotated_copy_in_scratch(b, rows, k, pad, mode, rounding):
     twice = M.mixfp4_quantize(x, tensor_scale=got[2], hadamard_block=b, hadamard_signs=sg, **opt)
     for g, w, t in zip(got, want, twice):
         assert torch.equal(g, w) and torch.equal(g, t)
+
+
+def _butterflies_fp64(x, b):
+    """Fast Walsh-Hadamard in fp64, stages in ascending order of the element bit."""
+    v = x.astype(np.float64).reshape(-1, b).copy()
+    for bit in range(b.bit_length() - 1):
+        t = v.reshape(-1, b >> (bit + 1), 2, 1 << bit)
+        v = np.stack([t[:, :, 0] + t[:, :, 1], t[:, :, 0] - t[:, :, 1]], 2).reshape(-1, b)
+    return v.reshape(x.shape)
+
+
+@pytest.mark.parametrize("b", [16, 64, 256])
+def test_stage_order_beyond_the_exact_span(b):
+    """Magnitudes 2^60 apart: large values that cancel in one stage and swallow
+    small ones in another, so the fp64 sums depend on the order of the stages,
+    which is that of the element bits.  b a power of 4: the scale is exact and
+    the sums are rounded once to bf16."""
+    import paper_2605_31035_amd as M
+    x = np.zeros((b.bit_length() * (b.bit_length() - 1), b), np.float32)
+    r = 0
+    for i in range(b.bit_length() - 1):                # the bit in which the large values differ
+        for j in range(b.bit_length() - 1):            # the bit of the small one
+            if i != j:
+                x[r, 0] = x[r, 1 << i] = 2.0 ** 60
+                x[r, 1 << j] = 3.0
+                r += 1
+    log(f"stage order b={b}")
+    y = M.mixfp4_hadamard(dev_bf16(W.f32_to_bf16_bits(x)), b)
+    m, e = np.frexp(_butterflies_fp64(x, b) / np.sqrt(b))
+    want = np.ldexp(np.rint(m * 256.0), e - 8)           # 8 significant bits, ties to even
+    np.testing.assert_array_equal(host(y.float()).astype(np.float64), want)
