@@ -58,20 +58,37 @@ bool scale_arg(PyObject* o, float** p) {
   return true;
 }
 
+// Lets other Python threads run, as a ctypes call does, while outputs are
+// allocated and the library is called: a launch may wait for room in the
+// queue, and a host function in front of it on the stream may need the
+// interpreter.  No Python object and no argument's tensor is touched
+// meanwhile (another thread may change it): shapes and addresses are read
+// before, and the caller's arguments keep the memory alive.
+class WithoutGil {
+ public:
+  WithoutGil() : state_(PyEval_SaveThread()) {}
+  ~WithoutGil() { PyEval_RestoreThread(state_); }
+  WithoutGil(const WithoutGil&) = delete;
+  WithoutGil& operator=(const WithoutGil&) = delete;
+
+ private:
+  PyThreadState* state_;
+};
+
 bool modes_active() {
   return at::impl::torch_function_mode_enabled() ||
          c10::impl::TorchDispatchModeTLS::any_modes_set();
 }
 
-at::Tensor empty(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like) {
-  return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
+at::Tensor empty(at::IntArrayRef shape, at::ScalarType type, c10::Device device) {
+  return at::empty(shape, at::TensorOptions().dtype(type).device(device));
 }
 
 uint8_t* bytes(const at::Tensor& t) { return static_cast<uint8_t*>(t.data_ptr()); }
 float* floats(const at::Tensor& t) { return static_cast<float*>(t.data_ptr()); }
 
-void* stream_of(const at::Tensor& t) {
-  return c10::hip::getCurrentHIPStream(t.device().index()).stream();
+void* stream_of(c10::Device device) {
+  return c10::hip::getCurrentHIPStream(device.index()).stream();
 }
 
 PyObject* triple(const at::Tensor& a, const at::Tensor& b, PyObject* c) {
@@ -92,20 +109,25 @@ PyObject* triple(const at::Tensor& a, const at::Tensor& b, const at::Tensor& c) 
 
 // A quantized operand (codes [rows, k/2], scales [rows, k/16], s32 or None).
 struct Operand {
-  const at::Tensor* codes = nullptr;
-  const at::Tensor* scales = nullptr;
+  uint8_t* codes = nullptr;
+  uint8_t* scales = nullptr;
   float* s32 = nullptr;
   int64_t rows = 0, k = 0;
+  c10::Device device = c10::Device(c10::kCPU);
 };
 bool operand(PyObject* o, Operand& q) {
   if (!PyTuple_CheckExact(o) || PyTuple_GET_SIZE(o) != 3) return false;
-  q.codes = plain(PyTuple_GET_ITEM(o, 0), at::kByte, 2);
-  if (!q.codes || !q.codes->is_contiguous()) return false;
-  q.rows = q.codes->size(0);
-  q.k = 2 * q.codes->size(1);
+  const at::Tensor* codes = plain(PyTuple_GET_ITEM(o, 0), at::kByte, 2);
+  if (!codes || !codes->is_contiguous()) return false;
+  q.rows = codes->size(0);
+  q.k = 2 * codes->size(1);
   if (q.k % 16 != 0) return false;
-  q.scales = matrix(PyTuple_GET_ITEM(o, 1), at::kByte, q.rows, q.k / 16);
-  return q.scales && scale_arg(PyTuple_GET_ITEM(o, 2), &q.s32);
+  const at::Tensor* scales = matrix(PyTuple_GET_ITEM(o, 1), at::kByte, q.rows, q.k / 16);
+  if (!scales) return false;
+  q.codes = bytes(*codes);
+  q.scales = bytes(*scales);
+  q.device = codes->device();
+  return scale_arg(PyTuple_GET_ITEM(o, 2), &q.s32);
 }
 
 template <typename Body>
@@ -160,20 +182,24 @@ PyObject* quantize(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const bool t = (flags & MIXFP4_TRANSPOSE) != 0;
     const int64_t orows = t ? k : rows, ok = t ? rows : k;
     if (ok % 16 != 0) return nullptr;
-    const at::Tensor codes = empty({orows, ok / 2}, at::kByte, *x);
-    const at::Tensor scales = empty({orows, ok / 16}, at::kByte, *x);
-    at::Tensor ts, scratch;
-    if (!given) {
-      ts = empty({1}, at::kFloat, *x);
-      const int64_t room = block >= 128 && !t && rows * k <= kRotatedElems ? 2 * rows * k : 0;
-      if (rows * k > (int64_t(1) << 17))
-        scratch = empty({mixfp4_quantize_scratch_bytes() + room}, at::kByte, *x);
+    const int64_t room = block >= 128 && !t && rows * k <= kRotatedElems ? 2 * rows * k : 0;
+    const uint16_t* xp = static_cast<const uint16_t*>(x->data_ptr());
+    const int64_t ldx = x->stride(0);
+    const c10::Device dev = x->device();
+    at::Tensor codes, scales, ts, scratch;
+    int st;
+    {
+      const WithoutGil released;
+      codes = empty({orows, ok / 2}, at::kByte, dev);
+      scales = empty({orows, ok / 16}, at::kByte, dev);
+      if (!given) ts = empty({1}, at::kFloat, dev);
+      if (!given && rows * k > (int64_t(1) << 17))
+        scratch = empty({mixfp4_quantize_scratch_bytes() + room}, at::kByte, dev);
+      st = mixfp4_quantize_ws(xp, rows, k, ldx, bytes(codes), bytes(scales),
+                              given ? given : floats(ts), flags, (int32_t)block, signs, seed,
+                              offset, scratch.defined() ? scratch.data_ptr() : nullptr,
+                              scratch.defined() ? scratch.numel() : 0, stream_of(dev));
     }
-    const int st = mixfp4_quantize_ws(
-        static_cast<const uint16_t*>(x->data_ptr()), rows, k, x->stride(0), bytes(codes),
-        bytes(scales), given ? given : floats(ts), flags, (int32_t)block, signs, seed, offset,
-        scratch.defined() ? scratch.data_ptr() : nullptr, scratch.defined() ? scratch.numel() : 0,
-        stream_of(*x));
     if (st != MIXFP4_OK) return nullptr;
     return given ? triple(codes, scales, args[1]) : triple(codes, scales, ts);
   });
@@ -190,12 +216,16 @@ PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (args[2] == Py_True &&
         mixfp4_gemm_auto_workspace_size(a.rows, w.rows, a.k, &need) != MIXFP4_OK)
       return nullptr;
-    const at::Tensor c = empty({a.rows, w.rows}, at::kFloat, *a.codes);
-    at::Tensor ws;
-    if (need > 0) ws = empty({need}, at::kByte, *a.codes);
-    const int st = mixfp4_gemm_auto(
-        bytes(*a.codes), bytes(*a.scales), a.s32, bytes(*w.codes), bytes(*w.scales), w.s32, a.rows,
-        w.rows, a.k, floats(c), need > 0 ? ws.data_ptr() : nullptr, need, stream_of(*a.codes));
+    at::Tensor c, ws;
+    int st;
+    {
+      const WithoutGil released;
+      c = empty({a.rows, w.rows}, at::kFloat, a.device);
+      if (need > 0) ws = empty({need}, at::kByte, a.device);
+      st = mixfp4_gemm_auto(a.codes, a.scales, a.s32, w.codes, w.scales, w.s32, a.rows, w.rows,
+                            a.k, floats(c), need > 0 ? ws.data_ptr() : nullptr, need,
+                            stream_of(a.device));
+    }
     return st == MIXFP4_OK ? THPVariable_Wrap(c) : nullptr;
   });
 }
@@ -211,14 +241,19 @@ PyObject* decode_step(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (w.k != k || w.rows <= 0 || m < 1 || m > 16 || k <= 0 || k % 64 != 0) return nullptr;
     const at::Tensor* sync = plain(args[2], at::kInt);
     if (!sync || sync->numel() != 4 || !sync->is_contiguous()) return nullptr;
-    const at::Tensor codes = empty({m, k / 2}, at::kByte, *x);
-    const at::Tensor scales = empty({m, k / 16}, at::kByte, *x);
-    const at::Tensor ts = empty({1}, at::kFloat, *x);
-    const at::Tensor c = empty({m, w.rows}, at::kFloat, *x);
-    const int st = mixfp4_decode_step(static_cast<const uint16_t*>(x->data_ptr()), m, k,
-                                      bytes(*w.codes), bytes(*w.scales), w.s32, w.rows,
-                                      bytes(codes), bytes(scales), floats(ts), floats(c),
-                                      static_cast<uint32_t*>(sync->data_ptr()), stream_of(*x));
+    const uint16_t* xp = static_cast<const uint16_t*>(x->data_ptr());
+    uint32_t* sp = static_cast<uint32_t*>(sync->data_ptr());
+    at::Tensor codes, scales, ts, c;
+    int st;
+    {
+      const WithoutGil released;
+      codes = empty({m, k / 2}, at::kByte, w.device);
+      scales = empty({m, k / 16}, at::kByte, w.device);
+      ts = empty({1}, at::kFloat, w.device);
+      c = empty({m, w.rows}, at::kFloat, w.device);
+      st = mixfp4_decode_step(xp, m, k, w.codes, w.scales, w.s32, w.rows, bytes(codes),
+                              bytes(scales), floats(ts), floats(c), sp, stream_of(w.device));
+    }
     if (st != MIXFP4_OK) return nullptr;
     PyObject* q = triple(codes, scales, ts);
     PyObject* o = THPVariable_Wrap(c);
@@ -240,9 +275,15 @@ PyObject* dequantize(PyObject*, PyObject* const* args, Py_ssize_t n) {
     const at::Tensor* scales = matrix(args[1], at::kByte, rows, k / 16);
     float* s32;
     if (!scales || !scale_arg(args[2], &s32)) return nullptr;
-    const at::Tensor out = empty({rows, k}, at::kFloat, *codes);
-    const int st = mixfp4_dequantize(bytes(*codes), bytes(*scales), s32, rows, k, floats(out),
-                                     stream_of(*codes));
+    const uint8_t *cp = bytes(*codes), *sp = bytes(*scales);
+    const c10::Device dev = codes->device();
+    at::Tensor out;
+    int st;
+    {
+      const WithoutGil released;
+      out = empty({rows, k}, at::kFloat, dev);
+      st = mixfp4_dequantize(cp, sp, s32, rows, k, floats(out), stream_of(dev));
+    }
     return st == MIXFP4_OK ? THPVariable_Wrap(out) : nullptr;
   });
 }
