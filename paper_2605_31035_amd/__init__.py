@@ -157,8 +157,11 @@ def mixfp4_quantize(x: torch.Tensor, tensor_scale: torch.Tensor | None = None,
         flags |= STOCHASTIC
     if transpose:
         flags |= TRANSPOSE
-    signs = _signs_arg(hadamard_signs, hadamard_block) if flags & (STOCHASTIC | TRANSPOSE) \
-        or hadamard_block else None
+    signs = None
+    if rounding == "nearest" and hadamard_block == 0 and not transpose:
+        hadamard_block = seed = offset = 0      # not used: whatever was given for them is taken
+    else:
+        signs = _signs_arg(hadamard_signs, hadamard_block)
     _keep, scr, scr_bytes = _scratch(rows * k if tensor_scale is None else 0, dev,
                                      hadamard_block >= 128 and not transpose)
     st = lib.mixfp4_quantize_ws(_ptr(x), rows, k, ldx, _ptr(codes), _ptr(scales), _ptr(ts),

@@ -65,3 +65,16 @@ def test_other_threads_run(name):
     t.join()
     torch.cuda.synchronize()
     assert seen and all(r is not None for r in kept)
+
+
+@pytest.mark.parametrize("unused", [dict(seed=None, offset=None), dict(seed=1.5),
+                                    dict(hadamard_block=0.0),
+                                    dict(hadamard_signs=torch.ones(16, dtype=torch.int8))])
+def test_unused_options_are_not_looked_at(unused):
+    """Rounding to nearest without rotation or transposition takes no draws, no
+    block and no signs: what stands in their place does not matter."""
+    import paper_2605_31035_amd as M
+    x = _x(5, 64)
+    log(f"unused options {unused}")
+    for g, w in zip(M.mixfp4_quantize(x, **unused), M.mixfp4_quantize(x)):
+        assert torch.equal(g, w)
