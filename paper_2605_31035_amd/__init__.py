@@ -183,22 +183,20 @@ _ROTATED_ELEMS = 1 << 26   # largest tensor whose rotated copy is taken as scrat
 def _scratch(elements: int, dev, rotated: bool = False):
     """(tensor to keep, pointer, bytes) of the scratch of a tensor-scale pass
     over so many elements (none where that pass is not a launch of its own),
-    with room for the rotated tensor if that memory is there.
+    with room for the rotated tensor; the call does without either where that
+    memory is not there.
     The caching allocator may hand it out again once this call returns, which
     the stream orders behind the launches."""
     if elements <= 1 << 17:
         return None, None, 0
-    words = _SCRATCH_WORDS
-    if rotated and elements <= _ROTATED_ELEMS:
+    for extra in ((elements // 2, 0) if rotated and elements <= _ROTATED_ELEMS else (0,)):
+        words = _SCRATCH_WORDS + extra
         try:
-            words += elements // 2
             t = torch.empty(words, dtype=torch.int32, device=dev)
         except torch.OutOfMemoryError:
-            words = _SCRATCH_WORDS
-            t = torch.empty(words, dtype=torch.int32, device=dev)
-    else:
-        t = torch.empty(words, dtype=torch.int32, device=dev)
-    return t, _ptr(t), 4 * words
+            continue
+        return t, _ptr(t), 4 * words
+    return None, None, 0
 
 
 def _signs_arg(signs, block):
@@ -378,7 +376,8 @@ def mixfp4_gemm(a, w, out: torch.Tensor | None = None, workspace=None) -> torch.
     (mixfp4_gemm), a contiguous uint8 CUDA tensor (mixfp4_gemm_ws with it),
     True (mixfp4_gemm_ws with a workspace of mixfp4_gemm_workspace_size bytes
     allocated here), or "auto" (mixfp4_gemm_auto: the route expected to be
-    the fastest, with the workspace it needs allocated here)."""
+    the fastest, with the workspace it needs allocated here; mixfp4_gemm where
+    that memory is not there)."""
     if out is None and (workspace is None or isinstance(workspace, str) and workspace == "auto"):
         r = native.gemm(a, w, workspace is not None)
         if r is not None:
@@ -410,8 +409,12 @@ def mixfp4_gemm(a, w, out: torch.Tensor | None = None, workspace=None) -> torch.
         auto = True
         need = ctypes.c_int64(0)
         _check(lib.mixfp4_gemm_auto_workspace_size(m, n, k, ctypes.byref(need)))
-        workspace = torch.empty(need.value, dtype=torch.uint8, device=ac.device) \
-            if need.value else None
+        workspace = None
+        if need.value:
+            try:
+                workspace = torch.empty(need.value, dtype=torch.uint8, device=ac.device)
+            except torch.OutOfMemoryError:
+                pass                            # the route that needs none
     elif workspace is True:
         workspace = torch.empty(max(1, mixfp4_gemm_workspace_size(m, n, k)), dtype=torch.uint8,
                                 device=ac.device)

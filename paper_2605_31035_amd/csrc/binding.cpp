@@ -139,8 +139,8 @@ PyObject* guarded(Body body) {
       if (PyErr_Occurred()) return nullptr;
     }
   } catch (const std::exception& e) {
-    // an allocation that failed: raised again, as torch raises it, by the
-    // Python path
+    // an allocation that failed: the Python path does without scratch or
+    // workspace, or raises as torch does
   }
   Py_RETURN_NONE;
 }
