@@ -26,7 +26,8 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmixfp4.so")
 NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["api.cpp", "quantize.hip", "quantize2d.hip", "dequantize.hip", "gemm.hip",
-           "gemm_f16.hip", "gemm_direct.hip", "decode_operand.hip", "quantize_variant.hip"]
+           "gemm_f16.hip", "gemm_direct.hip", "gemm_route.cpp", "decode_operand.hip",
+           "quantize_variant.hip"]
 
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 HIPCC = os.path.join(ROCM, "bin", "hipcc")

@@ -24,3 +24,11 @@ def test_help_lists_the_driver_options():
     assert r.returncode == 0
     for opt in ("--gpus", "--steps", "--warmup", "--only", "--no-cpu-baseline"):
         assert opt in r.stdout
+
+
+def test_gemm_traffic_is_reported():
+    """The traffic constants belong to the kernel source that is built: a change
+    of that file needs them measured again."""
+    sys.path.insert(0, ROOT)
+    import bench
+    assert bench.gemm_traffic_bytes() is not None
