@@ -336,11 +336,14 @@ int mixfp4_gemm_ws(const uint8_t *a_codes, const uint8_t *a_scales,
  * the two passes of mixfp4_gemm_ws.  The routes differ only in the order of
  * the fp32 sums.  With workspace == NULL, or less of it than
  * mixfp4_gemm_auto_workspace_size reports, the call computes what
- * mixfp4_gemm computes.  Arguments, alignment and errors as for
+ * mixfp4_gemm computes.  A W whose scales are not 4-byte aligned takes the
+ * two passes or no workspace: where it takes them, workspace_bytes has to be
+ * mixfp4_gemm_workspace_size's.  Arguments, alignment and errors as for
  * mixfp4_gemm_ws.
  *
  * mixfp4_gemm_auto_workspace_size - bytes of workspace that route needs (0:
- * none).  Host-only; errors as for mixfp4_gemm_workspace_size.
+ * none) for a W with 4-byte aligned scales.  Host-only; errors as for
+ * mixfp4_gemm_workspace_size.
  */
 int mixfp4_gemm_auto(const uint8_t *a_codes, const uint8_t *a_scales,
                      const float *a_tensor_scale, const uint8_t *w_codes,

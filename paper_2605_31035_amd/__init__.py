@@ -409,6 +409,9 @@ def mixfp4_gemm(a, w, out: torch.Tensor | None = None, workspace=None) -> torch.
         auto = True
         need = ctypes.c_int64(0)
         _check(lib.mixfp4_gemm_auto_workspace_size(m, n, k, ctypes.byref(need)))
+        if k % 64 == 0 and wsc.data_ptr() % 4:  # such scales are read in two passes or by no route
+            need.value = (mixfp4_gemm_workspace_size(m, n, k)
+                          if gemm_two_pass_preferred(m, n, k) else 0)
         workspace = None
         if need.value:
             try:

@@ -380,12 +380,10 @@ int mixfp4_gemm_auto(const uint8_t* a_codes, const uint8_t* a_scales, const floa
   if (workspace && !aligned(workspace, 256)) return MIXFP4_ERR_ALIGN;
   (void)hipGetLastError();
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const mixfp4::GemmPlan plan = mixfp4::gemm_plan(m, n, k);
-  // a W whose scale bytes are not word aligned is read by the other kernels
-  const bool direct = plan.route == mixfp4::GemmRoute::kDirect && aligned(w_scales, 4);
+  const mixfp4::GemmPlan plan = mixfp4::gemm_plan(m, n, k, aligned(w_scales, 4));
   if (workspace && plan.workspace > 0 && workspace_bytes >= plan.workspace) {
     uint8_t* ws = static_cast<uint8_t*>(workspace);
-    if (direct) {
+    if (plan.route == mixfp4::GemmRoute::kDirect) {
       const int e =
           launch_status(mixfp4::launch_decode_blocked(a_codes, a_scales, m, k, ws, s));
       if (e != MIXFP4_OK) return e;

@@ -213,7 +213,10 @@ PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (!operand(args[0], a) || !operand(args[1], w) || a.k != w.k || a.rows <= 0 || w.rows <= 0)
       return nullptr;
     int64_t need = 0;
-    if (args[2] == Py_True &&
+    const bool automatic = args[2] == Py_True;
+    if (automatic && (reinterpret_cast<uintptr_t>(w.scales) & 3u) != 0)
+      return nullptr;                    // rare: the Python path sizes its workspace
+    if (automatic &&
         mixfp4_gemm_auto_workspace_size(a.rows, w.rows, a.k, &need) != MIXFP4_OK)
       return nullptr;
     at::Tensor c, ws;

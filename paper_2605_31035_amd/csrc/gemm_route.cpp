@@ -45,11 +45,12 @@ float two_pass_us(int64_t m, int64_t n, int64_t k) {
 // kernel's masked loads lose to two passes from 17 rows on (17 x 11008 x
 // 4000 79 against 69 us, 512 x 11008 x 4000 220 against 79, 17 x 2048 x 1056
 // 23 against 22); below K = 512, where the launches count, and for K < 256,
-// two passes from m n / (m + n) = 1280 on.
-GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k) {
+// two passes from m n / (m + n) = 1280 on.  So too for a W whose scale bytes
+// are not word aligned, which the direct kernel does not read.
+GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool w_word_aligned) {
   if (!gemm_two_pass_applies(m, n, k)) return {GemmRoute::kNoWorkspace, 0, 0};
   const int64_t both = gemm_two_pass_workspace(m, n, k);
-  if (!gemm_direct_applies(m, n, k))
+  if (!w_word_aligned || !gemm_direct_applies(m, n, k))
     return (k % 64 != 0 && k >= 512) || m * n >= 1280 * (m + n)
                ? GemmPlan{GemmRoute::kTwoPass, 0, both}
                : GemmPlan{GemmRoute::kNoWorkspace, 0, 0};

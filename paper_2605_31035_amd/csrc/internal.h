@@ -193,7 +193,7 @@ struct GemmPlan {
   int tile;              // kDirect: the tile configuration
   int64_t workspace;     // bytes
 };
-GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k);
+GemmPlan gemm_plan(int64_t m, int64_t n, int64_t k, bool w_word_aligned = true);
 // One-launch decode step (A[m, k] bf16 row-major, quantized in the launch,
 // then C = A W^T): applies for 1 <= m <= 16 and k % 64 == 0 (the decode-
 // shape GEMM's K split); `sync` is 4 zeroed uint32 on the device, returned

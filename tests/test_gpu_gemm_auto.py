@@ -116,3 +116,26 @@ def test_k_of_32_takes_two_passes(m, n, k):
     c = M.mixfp4_gemm(a, w, workspace="auto")
     assert torch.equal(c, M.mixfp4_gemm(a, w, workspace=True))
     _check(host(c), qa, qw, m, n)
+
+
+@pytest.mark.parametrize("m,n,k,two", [(2048, 4096, 512, True), (1300, 100, 1024, False),
+                                       (4096, 4096, 4096, True), (200, 1000, 544, True)])
+def test_unaligned_w_scales(m, n, k, two):
+    """W's scale bytes off a word: the direct GEMM does not read them; products
+    that pay for two passes still take them (they write the workspace)."""
+    import paper_2605_31035_amd as M
+    from tests._gpu import gpu_quantize
+    log(f"unaligned W scales {m}x{n}x{k}")
+    a, w = gpu_quantize(W.adversarial(m, m, k)), gpu_quantize(W.adversarial(n, n, k))
+    buf = torch.empty(w[1].numel() + 1, dtype=torch.uint8, device="cuda")
+    shifted = buf[1:].view(w[1].shape).copy_(w[1])
+    assert shifted.data_ptr() % 4 == 1
+    ws = torch.zeros(M.mixfp4_gemm_workspace_size(m, n, k), dtype=torch.uint8, device="cuda")
+    c = torch.full((m, n), float("nan"), device="cuda")
+    p = M._ptr
+    assert M.lib.mixfp4_gemm_auto(p(a[0]), p(a[1]), p(a[2]), p(w[0]), p(shifted), p(w[2]), m, n, k,
+                                  p(c), p(ws), ws.numel(), M._stream(c.device)) == 0
+    assert bool(ws.any()) == two
+    want = M.mixfp4_gemm(a, w, workspace=True if two else None)
+    assert torch.equal(c, want)
+    assert torch.equal(M.mixfp4_gemm(a, (w[0], shifted, w[2]), workspace="auto"), want)
