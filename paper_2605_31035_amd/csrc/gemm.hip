@@ -34,6 +34,7 @@
 // [16 B]; the 64 lanes of a fragment read and the threads of a decode write
 // both hit consecutive 16-byte words.  Rows beyond m / n and blocks beyond k
 // decode as zeros; stores are masked.
+#include <cmath>
 #include <type_traits>
 
 #include "decode.h"
@@ -927,6 +928,39 @@ hipError_t launch_gemm(const uint8_t* a_codes, const uint8_t* a_scales, const fl
                                        c, n, stream);
   return launch_tile<128, 128, 2, 2>(a_codes, a_scales, a_ts, w_codes, w_scales, w_ts, m, n, k,
                                      c, n, stream);
+}
+
+// Fitted to 2900 device times, m 17 to 4096, n 512 to 28672, 11 K from 256 to
+// 11008 and 10 with K % 64 = 32 (K up to 4096: half of them within 2% for
+// K % 64 == 0, 95% within 7; K % 64 = 32, one round: 5 and 14).  Per 4096 of
+// K a round of 128 x 128 tiles takes 39 to 44 us (67 to 69 with two on a CU),
+// one of 128 x 256 72, one of 256 x 256 73 to 115; C leaves at 5 TB/s, partly
+// beside the next tiles.  With K % 64 = 32 the masked loads cost by the share
+// of real rows in a tile; more than one round of them is slower than two
+// passes from K = 512 on and is not modelled.
+float gemm_fused_us(int64_t m, int64_t n, int64_t k) {
+  const float cus = (float)compute_units(), kf = (float)k / 4096.0f;
+  const float c_us = (float)m * (float)n * 4.0f / 5e6f;
+  const int64_t tm = (m + 255) / 256, tn = (n + 255) / 256, rows = (m + 127) / 128;
+  const int64_t tiles256 = tm * tn, tiles128x256 = rows * tn;
+  auto large = [&](int64_t tiles) {                // 256 x 256
+    const float full = std::floor((float)tiles / cus), f = (float)tiles / cus - full;
+    return 3.5f + full * 115.0f * kf + (f > 0.0f ? (73.0f + 32.0f * f) * kf : 0.0f);
+  };
+  if ((float)(4 * tiles256) >= 3.0f * cus) {
+    const int64_t c = (int64_t)cus, nt1 = (tiles256 / c) * c / tm, rest = 2 * tm * (tn - nt1);
+    if (nt1 > 0 && nt1 < tn && rest <= c)          // whole rounds, then a launch of 128 x 256 tiles
+      return 3.5f + std::ceil((float)(tm * nt1) / cus) * 115.0f * kf + 7.5f + 72.0f * kf + c_us;
+    return large(tiles256) + c_us;
+  }
+  if ((float)(4 * tiles128x256) >= 3.0f * cus)
+    return 7.5f + std::ceil((float)tiles128x256 / cus) * 72.0f * kf + 0.5f * c_us;
+  const float w = (float)(rows * ((n + 127) / 128)) / cus;   // workgroups per CU, at most 2
+  if (k % 64 != 0) {
+    const float real = (float)m / (float)(128 * rows);
+    return 3.2f + (77.0f + 25.0f * real + 26.0f * w + 37.0f * real * w) * kf;
+  }
+  return 6.5f + (w <= 1.0f ? 39.0f + 5.0f * w : 67.0f + 2.0f * (w - 1.0f)) * kf + 0.8f * c_us;
 }
 
 }  // namespace mixfp4

@@ -484,7 +484,7 @@ bool gemm_direct_applies(int64_t m, int64_t n, int64_t k) {
   return gemm_two_pass_applies(m, n, k) && k % kStepK64 == 0 && k >= 256;
 }
 
-int gemm_direct_tile(int64_t m, int64_t n, int64_t k, float* us) {
+int gemm_direct_tile(int64_t m, int64_t n, int64_t k, float* us, int* rounds) {
   const int64_t cus = compute_units();
   int best = -1;
   float cost = 0.0f;
@@ -497,6 +497,9 @@ int gemm_direct_tile(int64_t m, int64_t n, int64_t k, float* us) {
     }
   }
   *us = cost;
+  const DirectTile& t = kTiles[best];
+  const int64_t wgs = ((m + t.rows - 1) / t.rows) * ((n + t.cols - 1) / t.cols);
+  *rounds = (int)((wgs + cus * t.per_cu - 1) / (cus * t.per_cu));
   return best;
 }
 

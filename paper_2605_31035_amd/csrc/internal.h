@@ -180,12 +180,15 @@ hipError_t launch_gemm_decoded(const uint8_t* ablk, const float* a_ts, const uin
 // The GEMM on a decoded A (blocked layout, rows padded to 256) and a packed
 // W with 4-byte aligned scales: applies for m > 16, k % 64 == 0, k >= 256.
 // gemm_direct_tile picks the tile configuration and reports its expected
-// time in us; its result goes to launch_gemm_direct.
+// time in us (at K near 4096; see gemm_plan) and its rounds of workgroups;
+// its result goes to launch_gemm_direct.
 bool gemm_direct_applies(int64_t m, int64_t n, int64_t k);
-int gemm_direct_tile(int64_t m, int64_t n, int64_t k, float* us);
+int gemm_direct_tile(int64_t m, int64_t n, int64_t k, float* us, int* rounds);
 hipError_t launch_gemm_direct(int tile, const uint8_t* ablk, const float* a_ts,
                               const uint8_t* w_codes, const uint8_t* w_scales, const float* w_ts,
                               int64_t m, int64_t n, int64_t k, float* c, hipStream_t stream);
+// Expected time in us of launch_gemm for m > 16 and 256 <= k <= 4096.
+float gemm_fused_us(int64_t m, int64_t n, int64_t k);
 // The route expected to be the fastest, and the workspace it needs.
 enum class GemmRoute { kNoWorkspace, kDirect, kTwoPass };
 struct GemmPlan {

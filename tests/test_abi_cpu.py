@@ -381,7 +381,9 @@ def test_gemm_auto_workspace(lib):
     assert lib.mixfp4_gemm_auto_workspace_size(64, 4096, 4096, None) == 1
     assert lib.mixfp4_gemm_auto_workspace_size(64, 4096, 24, ctypes.byref(b)) == 2
     for m, n, k, want in [(16, 28672, 8192, 0), (64, 64, 48, 0), (64, 4096, 192, 0),
-                          (64, 4096, 480, 0), (17, 256, 544, 512 * 544 * 2),
+                          (64, 4096, 480, 0), (17, 256, 544, 0), (17, 8192, 1056, 0),
+                          (17, 256, 1568, 512 * 1568 * 2), (768, 4096, 1024, 0),
+                          (1024, 2048, 512, 0), (3000, 1024, 1024, 0),
                           (64, 4096, 4096, 256 * 4096 * 2),
                           (16384, 8192, 8192, (16384 + 8192) * 8192 * 2)]:
         assert lib.mixfp4_gemm_auto_workspace_size(m, n, k, ctypes.byref(b)) == 0

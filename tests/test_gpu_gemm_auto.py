@@ -43,24 +43,8 @@ def _need(m, n, k):
     return b.value
 
 
-# One row or more per tile configuration (rows x columns of a workgroup),
-# with ragged edges, every K remainder of 256 and shares of K that are empty
-# (256) or differ by a step.
-@pytest.mark.parametrize("m,n,k", [
-    (17, 33, 256), (64, 4090, 576), (33, 130, 320), (31, 8200, 320), (129, 17003, 320),   # 32 x 32
-    (31, 14300, 3008), (17, 16300, 4096),                  # 32 x 64
-    (100, 4090, 4096), (128, 4090, 3008),                  # 64 x 32
-    (33, 9001, 320), (64, 8200, 1024), (64, 28672, 576),   # 64 x 64
-    (129, 17003, 256), (33, 17003, 1024),                  # 64 x 128
-    (65, 8200, 576), (509, 11001, 320),                    # 128 x 64
-    (65, 17003, 384), (509, 16300, 256),                   # 128 x 128
-    (500, 11001, 1024),                                    # 128 x 256, K halved over the waves
-    (129, 28672, 320), (509, 28672, 576),                  # 128 x 256, two workgroups per CU
-])
-def test_direct_tiles(m, n, k):
+def _auto_against_oracle(m, n, k):
     import paper_2605_31035_amd as M
-    log(f"direct gemm m={m} n={n} k={k}")
-    assert _need(m, n, k) == (m + 255) // 256 * 256 * k * 2     # A decoded, W packed
     if n * k < 1 << 22:
         qa, qw = Q.quantize(W.adversarial(m + 3 * k, m, k)), Q.quantize(W.adversarial(n + k, n, k))
         a, w = _dev(qa), _dev(qw)
@@ -105,10 +89,43 @@ def test_direct_falls_back():
     _check(host(call(odd, need)), qa, qw, m, n)
 
 
-@pytest.mark.parametrize("m,n,k", [(17, 33, 544), (70, 300, 1056)])
+# One row or more per tile configuration (rows x columns of a workgroup),
+# with ragged edges, every K remainder of 256 and shares of K that differ by a
+# step.
+@pytest.mark.parametrize("m,n,k", [
+    (17, 33, 576), (64, 4090, 576), (33, 130, 704), (500, 1001, 832),      # 32 x 32
+    (31, 14300, 3008), (17, 16300, 4096),                  # 32 x 64
+    (100, 4090, 4096), (128, 4090, 3008),                  # 64 x 32
+    (33, 9001, 640), (64, 8200, 1024), (129, 4001, 640), (500, 1999, 832),  # 64 x 64
+    (33, 17003, 1024), (33, 17003, 1280),                  # 64 x 128
+    (65, 8235, 704),                                       # 128 x 64
+    (67, 16907, 3072), (647, 10782, 512), (131, 24372, 1536),              # 128 x 128
+    (133, 18715, 1280), (500, 11001, 2048),                # 128 x 256, K halved over the waves
+    (257, 22173, 576), (300, 21903, 640),                  # 128 x 256, two workgroups per CU
+])
+def test_direct_tiles(m, n, k):
+    log(f"direct gemm m={m} n={n} k={k}")
+    assert _need(m, n, k) == (m + 255) // 256 * 256 * k * 2     # A decoded, W packed
+    _auto_against_oracle(m, n, k)
+
+
+# Short K and many rows or columns: one launch of the fused kernel, no workspace.
+@pytest.mark.parametrize("m,n,k", [
+    (17, 33, 256), (33, 130, 320), (31, 8200, 320), (129, 17003, 320), (33, 9001, 320),
+    (64, 28672, 576), (129, 17003, 256), (65, 8200, 576), (509, 11001, 320), (65, 17003, 384),
+    (509, 16300, 256), (500, 11001, 1024), (129, 28672, 320), (509, 28672, 576),
+    (768, 4096, 1024), (1024, 2048, 512),
+    (17, 33, 544), (17, 8192, 1056), (100, 600, 800)])          # K % 64 = 32
+def test_short_k_takes_no_workspace(m, n, k):
+    log(f"auto without workspace m={m} n={n} k={k}")
+    assert _need(m, n, k) == 0
+    _auto_against_oracle(m, n, k)
+
+
+@pytest.mark.parametrize("m,n,k", [(70, 300, 1056), (17, 2048, 4000)])
 def test_k_of_32_takes_two_passes(m, n, k):
-    """K % 64 = 32 from 512 on: both operands decoded, bit for bit as with the
-    workspace given."""
+    """K % 64 = 32 where W's decode is the smaller cost: both operands decoded,
+    bit for bit as with the workspace given."""
     import paper_2605_31035_amd as M
     assert _need(m, n, k) == M.mixfp4_gemm_workspace_size(m, n, k) > 0
     qa, qw = Q.quantize(W.adversarial(m, m, k)), Q.quantize(W.adversarial(n, n, k))
@@ -119,7 +136,7 @@ def test_k_of_32_takes_two_passes(m, n, k):
 
 
 @pytest.mark.parametrize("m,n,k,two", [(2048, 4096, 512, True), (1300, 100, 1024, False),
-                                       (4096, 4096, 4096, True), (200, 1000, 544, True)])
+                                       (4096, 4096, 4096, True), (200, 1000, 1056, True)])
 def test_unaligned_w_scales(m, n, k, two):
     """W's scale bytes off a word: the direct GEMM does not read them; products
     that pay for two passes still take them (they write the workspace)."""
