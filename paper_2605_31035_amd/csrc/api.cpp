@@ -90,7 +90,8 @@ int quantize_impl(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8
   if (transpose) {
     if (empty) {
       if (given) return MIXFP4_OK;
-      return launch_status(mixfp4::launch_tensor_scale(x, 0, k, ldx, nullptr, 0, tensor_scale, s));
+      return launch_status(mixfp4::launch_tensor_scale(x, 0, k, ldx, nullptr, 0, tensor_scale, s,
+                                                         mixfp4::kKeptNever));
     }
     const int64_t nscr = rows * (k / mixfp4::kBlock);
     if (!given) {
@@ -98,7 +99,7 @@ int quantize_impl(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8
           opt.had ? mixfp4::launch_tensor_scale_t_rotated(x, rows, k, ldx, opt.hp, scales, nscr,
                                                           tensor_scale, s, own, &in)
                   : mixfp4::launch_tensor_scale(x, rows, k, ldx, scales, nscr, tensor_scale, s,
-                                                own, &in);
+                                                mixfp4::kKeptTransposed, own, &in);
       const int st = launch_status(e);
       if (st != MIXFP4_OK) return st;
     }
@@ -118,7 +119,7 @@ int quantize_impl(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, uint8
                                                       tensor_scale, s, own, &in, y)
                 : mixfp4::launch_tensor_scale(x, empty ? 0 : rows, k, ldx,
                                               empty ? nullptr : scales, nscr, tensor_scale, s,
-                                              own, &in);
+                                              mixfp4::kKeptNever, own, &in);
     const int st = launch_status(e);
     if (st != MIXFP4_OK) return st;
     if (y) {
@@ -202,7 +203,7 @@ int mixfp4_quantize_2d(const uint16_t* w, int64_t rows, int64_t k, int64_t ldw, 
   if (!given) {
     const int st = launch_status(mixfp4::launch_tensor_scale(
         w, empty ? 0 : rows, k, ldw, empty ? nullptr : scales,
-        empty ? 0 : rows * (k / mixfp4::kBlock), tensor_scale, s));
+        empty ? 0 : rows * (k / mixfp4::kBlock), tensor_scale, s, mixfp4::kKept2d));
     if (st != MIXFP4_OK) return st;
   }
   if (empty) return MIXFP4_OK;
@@ -250,7 +251,7 @@ int mixfp4_quantize_variant(const uint16_t* x, int64_t rows, int64_t k, int64_t 
   if ((flags & MIXFP4_SCALE_GIVEN) == 0u) {
     const int st = launch_status(mixfp4::launch_tensor_scale(
         x, empty ? 0 : rows, k, ldx, empty ? nullptr : scales, empty ? 0 : rows * (k / block),
-        tensor_scale, s));
+        tensor_scale, s, mixfp4::kKeptVariant));
     if (st != MIXFP4_OK) return st;
   }
   if (empty) return MIXFP4_OK;
@@ -467,7 +468,7 @@ int mixfp4_quantize_decode_ws(const uint16_t* x, int64_t rows, int64_t k, int64_
   if ((flags & MIXFP4_SCALE_GIVEN) == 0u) {
     const int st = launch_status(mixfp4::launch_tensor_scale(
         x, empty ? 0 : rows, k, ldx, empty ? nullptr : scales,
-        empty ? 0 : rows * (k / mixfp4::kBlock), tensor_scale, s,
+        empty ? 0 : rows * (k / mixfp4::kBlock), tensor_scale, s, mixfp4::kKeptDecode,
         own_partials(scratch, scratch_bytes), &in));
     if (st != MIXFP4_OK) return st;
   }

@@ -94,6 +94,21 @@ inline int64_t compute_units() {
 }
 
 // Launchers: shapes are validated by the ABI layer before these are called.
+// Sizes of a contiguous X in MB that its maximum pass leaves in the infinity
+// cache for the pass behind it (one or two ranges; figures at
+// amax_stream_kernel).
+struct KeptRange {
+  int64_t from = 1, to = 0, from2 = 1, to2 = 0;
+  bool holds(int64_t bytes) const {
+    const auto in = [&](int64_t lo, int64_t hi) {
+      return bytes >= lo * (1 << 20) && bytes <= hi * (1 << 20);
+    };
+    return in(from, to) || in(from2, to2);
+  }
+};
+constexpr KeptRange kKeptNever{}, kKeptTransposed{32, 120}, kKept2d{32, 100, 148, 168},
+    kKeptDecode{32, 72}, kKeptVariant{32, 96};
+
 // Tensor scale s32 = max|X| / 2688 (1.0 for all-zero X) into *tensor_scale.
 // `scratch` (may be NULL) is device memory of `scratch_bytes` that the call
 // may overwrite before the quantize kernel writes it (the scale-byte output).
@@ -102,7 +117,7 @@ inline int64_t compute_units() {
 // quantize kernel to do it, and otherwise to read *tensor_scale.
 hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k,
                                int64_t ldx, uint8_t* scratch, int64_t scratch_bytes,
-                               float* tensor_scale, hipStream_t stream,
+                               float* tensor_scale, hipStream_t stream, KeptRange kept,
                                uint32_t* partials = nullptr, ScaleIn* in = nullptr);
 // Tensor scale of the rotated tensor (the amax pass of a rotate-and-quantize
 // call); same contract as launch_tensor_scale.  With y (rows * k values) the

@@ -88,13 +88,25 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
 // contiguous memory, with the non-temporal hint (X is read once here), the
 // next window's loads in flight while this one is reduced.  Windows past the
 // end read zeros (buffer range check), which leave the maximum unchanged.
-// X of 32 to 160 MB is loaded without the hint, so that the quantize pass
-// finds it in the 256 MB infinity cache: a 2D weight of 11008 x 4096 62.3 ->
-// 57.9 us in a loop over three of them (its second pass 45 -> 39 us), 4096 x
-// 11008 45.9 -> 45.4.  Smaller ones stay there anyway, and the pass itself is
-// faster with the hint (1537 x 4096: 14.4 against 14.8 us).
+// Where X is of a size in KeptRange it is loaded without the hint, so that the
+// pass behind finds it in the 256 MB infinity cache.  How long that pays
+// depends on what that pass writes beside it (us with -> without the hint, in
+// a loop over three tensors, 24 to 320 MB in steps of 4 to 32):
+//   2D, both layouts: 32 MB 28.1 -> 25.3, 64 MB 47.0 -> 40.2, 96 MB 66.6 ->
+//     57.5, 104 MB 71.2 -> 73.0, 128 MB 85.5 -> 92.1, 140 MB 93.2 -> 95.7,
+//     160 MB 106 -> 96, 168 MB 110 -> 110, 200 MB 131 -> 141
+//   decode fused: 32 MB 26.8 -> 26.0, 64 MB 45.0 -> 42.8, 72 MB 49.4 -> 48.6,
+//     80 MB 54.4 -> 55.3, 128 MB 82.4 -> 96.1
+//   transposed: 32 MB 23.9 -> 22.8, 120 MB 65.5 -> 62.3, 152 MB 82.3 -> 83.8
+//   variant: 32 MB 29.1 -> 28.7, 96 MB 71.9 -> 71.7, 128 MB 93.3 -> 94.7
+//   1D, never: 32 MB 21.1 -> 21.0, 64 MB 34.7 -> 34.1, 160 MB 74.7 -> 73.0,
+//     but the GEMM behind pays more for X in the cache (linear 4096 x 11008 x
+//     5008 1202 -> 1229 us, 5120 x 8192 x 4096 338 -> 343, 8192 x 4096 x 8208
+//     1343 -> 1375), and with stochastic rounding the call itself loses
+//     (117 MB 82.1 -> 82.9, backward 4096 x 14336 x 4096 1044 -> 1058)
+// Smaller ones stay there anyway, and the pass itself is faster with the hint
+// (1537 x 4096: 14.4 against 14.8 us).
 constexpr int kNonTemporal = 2;
-constexpr int64_t kKeptFrom = int64_t(32) << 20, kKeptTo = int64_t(160) << 20;
 constexpr int kAmaxWindow = 256;      // vectors of 8 bf16 per wave per iteration
 
 template <int kAux>
@@ -598,7 +610,7 @@ HadamardParams hadamard_params(int b, const int8_t* signs) {
 
 hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx,
                                uint8_t* scratch, int64_t scratch_bytes, float* tensor_scale,
-                               hipStream_t stream, uint32_t* own, ScaleIn* in) {
+                               hipStream_t stream, KeptRange kept, uint32_t* own, ScaleIn* in) {
   const int64_t total = rows * (k >> 3);
   if (ldx == k) {
     // one window of 4 KB per wave, four waves per workgroup, at most 4
@@ -609,7 +621,7 @@ hipError_t launch_tensor_scale(const uint16_t* x, int64_t rows, int64_t k, int64
     const int g = (int)(wanted < resident ? (wanted > 0 ? wanted : 1) : resident);
     return tensor_scale_with(total, g, scratch, scratch_bytes, tensor_scale, stream, own, in,
                              [&](int grid, uint32_t* partials, uint32_t* out) {
-                               if (total * 16 >= kKeptFrom && total * 16 <= kKeptTo)
+                               if (kept.holds(total * 16))
                                  amax_stream_kernel<0><<<grid, kThreads, 0, stream>>>(
                                      x, total, partials, out);
                                else
