@@ -29,8 +29,12 @@ __device__ __forceinline__ float tensor_scale_of(uint32_t amax_bf16_bits) {
 // launch of its own between the maximum pass and this one (4 KB from L2
 // against a kernel boundary): 1537 x 4096 14.6 -> 13.4 us for the two passes,
 // the transposed 2048 x 11008 55.8 -> 54.0 us.
+// A given scale is read through the constant address space (no launch writes
+// it beside this one): a scalar load that the compiler may issue at once,
+// ahead of the scale table's divisions and LDS stores.
 __device__ __forceinline__ float load_tensor_scale(const ScaleIn& in) {
-  if (!in.partials) return *in.s32;
+  typedef const __attribute__((address_space(4))) float ConstFloat;
+  if (!in.partials) return *(ConstFloat*)(uintptr_t)in.s32;
   __shared__ uint32_t wave_max[16];
   uint32_t m = 0u;
   for (int i = (int)threadIdx.x; i < in.count; i += (int)blockDim.x) m = max(m, in.partials[i]);
