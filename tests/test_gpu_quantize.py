@@ -108,10 +108,11 @@ def test_tensor_scale_fallback(exp):
                                         (16, 8192, 0), (3, 48, 8), (100, 1024, 64),
                                         (2049, 8192, 0)])
 def test_small_and_large_compute_paths(rows, k, pad):
-    """Tensors of at most 2^18 elements get their tensor scale and codes in one
-    launch (every workgroup reduces max|X| itself); larger ones take the
-    amax / reduce / quantize sequence.  Both sides of the threshold, strided
-    rows included, must give the oracle's bits."""
+    """Tensors of at most 2^17 elements (16 x 8192 is the largest here) get their
+    tensor scale and codes in one launch (every workgroup reduces max|X|
+    itself); larger ones take a pass for the maximum first.  Strided rows
+    included, all must give the oracle's bits; the edges of the one-launch
+    kernel's sizes are in test_gpu_one_launch_quantize."""
     bits = W.adversarial(rows * 7 + k, rows, k)
     _assert_same(bits, ldx_pad=pad, label=f"compute path {rows}x{k}")
 

@@ -47,8 +47,9 @@ def _check_quant(got, ref, label):
                                             (65, 4096, None, 0), (257, 80, 0.37, 0),
                                             (33, 64, None, 8), (300, 1024, 1.5, 24)])
 def test_stochastic_rounding(mode, omode, rows, k, s32, pad):
-    """Small one-launch path (COMPUTE, <= 2^18 elements), two-pass path,
-    given s32, strided rows; seed and offset with high words set."""
+    """Small one-launch path (COMPUTE, <= 2^17 elements: 3 x 48 and 33 x 64; its
+    other sizes are in test_gpu_one_launch_quantize), two-pass path, given
+    s32, strided rows; seed and offset with high words set."""
     import paper_2605_31035_amd as M
     bits = W.adversarial(rows + k, rows, k)
     label = f"sr {mode} {rows}x{k} s32={s32} pad={pad}"
