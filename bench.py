@@ -81,6 +81,20 @@ def gemm_traffic_bytes():
     return round((t["fetch_kib"] * t["fetch_scale"] + t["write_kib"] * t["write_scale"]) * 1024)
 
 
+def auto_route(m, n, k):
+    """The route of mixfp4_gemm(..., workspace="auto"), told by its workspace."""
+    import ctypes
+
+    import paper_2605_31035_amd as M
+    need = ctypes.c_int64(0)
+    assert M.lib.mixfp4_gemm_auto_workspace_size(m, n, k, ctypes.byref(need)) == 0
+    if need.value == 0:
+        return "fused"
+    return ("two-pass (both operands decoded in the call)"
+            if need.value == M.mixfp4_gemm_workspace_size(m, n, k) else
+            "direct (A decoded in the call, W read packed)")
+
+
 def log(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
@@ -409,13 +423,9 @@ def measure_train(M, torch, dev, iters: int = 10) -> dict:
                          .astype(np.int8), device=dev)
     names = ["quantize X", "quantize_2d W", "fprop gemm", "quantize dY (SR)", "dgrad gemm",
              "quantize dY^T (RHT16, SR)", "quantize X^T (RHT16)", "wgrad gemm"]
-    # every GEMM on its preferred route (gemm_two_pass_preferred), the
-    # two-pass workspace allocated once before timing
+    # every GEMM on the library's own route
     shapes = {"fprop": (tok, d_out, d_in), "dgrad": (tok, d_in, d_out), "wgrad": (d_out, d_in, tok)}
-    two = {g: M.gemm_two_pass_preferred(*mnk) for g, mnk in shapes.items()}
-    ws_bytes = max([M.mixfp4_gemm_workspace_size(*shapes[g]) for g in shapes if two[g]] + [1])
-    ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
-    wsp = {g: (ws if two[g] else None) for g in shapes}
+    wsp = dict.fromkeys(shapes, "auto")
 
     def step(e=None, it=0):
         def mark(i):
@@ -475,8 +485,7 @@ def measure_train(M, torch, dev, iters: int = 10) -> dict:
         "us": {n: round(v * 1e3, 2) for n, v in zip(names, spans)},
         "gemm_TFLOPs": {n: round(flops / (spans[j] * 1e-3) / 1e12, 1)
                         for n, j in (("fprop", 2), ("dgrad", 4), ("wgrad", 7))},
-        "gemm_path": {g: ("two-pass (both operands decoded in the call)" if two[g] else "fused")
-                      for g in shapes},
+        "gemm_path": {g: auto_route(*mnk) for g, mnk in shapes.items()},
         "quantize_GBps": {n: round(el * QUANT_BYTES_PER_ELEM / (spans[j] * 1e-3) / 1e9, 1)
                           for n, j, el in (("quantize_2d W (COMPUTE)", 1, d_out * d_in),
                                            ("quantize dY^T (COMPUTE, RHT16, SR)", 5, tok * d_out),
@@ -486,7 +495,7 @@ def measure_train(M, torch, dev, iters: int = 10) -> dict:
             "us": round(q2d_us, 2), "GBps": round(q2d_gbps, 1), "bytes_per_elem": 3.125,
             "hbm_frac": round(q2d_gbps / 8000.0, 4)},
     }
-    del X, Wt, dY, t, ws
+    del X, Wt, dY, t
     torch.cuda.empty_cache()
     return out
 

@@ -145,14 +145,15 @@ int mixfp4_quantize_ex(const uint16_t *x, int64_t rows, int64_t k, int64_t ldx,
 
 /*
  * mixfp4_quantize_ws, mixfp4_quantize_decode_ws - mixfp4_quantize_ex and
- * mixfp4_quantize_decode with caller-owned device scratch for the tensor-scale pass: with at least
- * mixfp4_quantize_scratch_bytes() (4096) bytes, 4-byte aligned, the
- * per-workgroup maxima are kept there and folded by the quantize kernel,
- * which saves a launch.  A quantization rotated by 128 or 256 that computes its
- * scale (not transposed), with 2 * rows * k bytes more than that, 16-byte aligned, keeps
- * the rotated tensor there instead of rotating X twice.  Outputs are the same, bit for bit.  The scratch's
- * contents on entry are ignored and on return unspecified; it must not be
- * used by anything else until the call's work is done (same stream is
+ * mixfp4_quantize_decode with caller-owned device scratch for the
+ * tensor-scale pass: with at least mixfp4_quantize_scratch_bytes() (4096)
+ * bytes, 4-byte aligned, the per-workgroup maxima are kept there and folded
+ * by the quantize kernel, which saves a launch.  A quantization rotated by
+ * 128 or 256 that computes its scale (not transposed), with 2 * rows * k
+ * bytes more than that, 16-byte aligned, keeps the rotated tensor there
+ * instead of rotating X twice.  Outputs are the same, bit for bit.  The
+ * scratch's contents on entry are ignored and on return unspecified; it must
+ * not be used by anything else until the call's work is done (same stream is
  * enough).  scratch == NULL or less of it: as the function without _ws;
  * misaligned: MIXFP4_ERR_ALIGN; scratch_bytes < 0: MIXFP4_ERR_SHAPE.
  */
@@ -330,11 +331,11 @@ int mixfp4_gemm_ws(const uint8_t *a_codes, const uint8_t *a_scales,
 /*
  * mixfp4_gemm_auto - mixfp4_gemm with caller-supplied device workspace, on
  * the route expected to be the fastest for the shape: without workspace
- * (decode shapes, K % 32 != 0 and small products of K < 512), with A
- * decoded once into the workspace and W decoded on its way into the matrix
- * instructions (m > 16 up to about a thousand rows, K % 64 == 0, K >= 256), or
- * the two passes of mixfp4_gemm_ws.  The routes differ only in the order of
- * the fp32 sums.  With workspace == NULL, or less of it than
+ * (m <= 16, K % 32 != 0, and products of short K, up to about 1000 where m or
+ * n is large), with A decoded once into the workspace and W decoded on its
+ * way into the matrix instructions (m > 16 up to about a thousand rows,
+ * K % 64 == 0, K >= 256), or the two passes of mixfp4_gemm_ws.  The routes
+ * differ only in the order of the fp32 sums.  With workspace == NULL, or less of it than
  * mixfp4_gemm_auto_workspace_size reports, the call computes what
  * mixfp4_gemm computes.  A W whose scales are not 4-byte aligned takes the
  * two passes or no workspace: where it takes them, workspace_bytes has to be

@@ -182,7 +182,8 @@ _ROTATED_ELEMS = 1 << 26   # largest tensor whose rotated copy is taken as scrat
 
 def _scratch(elements: int, dev, rotated: bool = False):
     """(tensor to keep, pointer, bytes) of the scratch of a tensor-scale pass
-    over so many elements (none where that pass is not a launch of its own),
+    over so many elements (none up to 2^17: a plain call of that size is one
+    launch; a rotated, transposed or decoding one folds its maxima itself),
     with room for the rotated tensor; the call does without either where that
     memory is not there.
     The caching allocator may hand it out again once this call returns, which
@@ -358,7 +359,10 @@ def mixfp4_gemm_workspace_size(m: int, n: int, k: int) -> int:
 
 def gemm_two_pass_preferred(m: int, n: int, k: int) -> bool:
     """Whether the two-pass GEMM (both operands decoded once, then the fp16
-    GEMM) is expected to beat the fused kernel for C[m, n] = A W^T: the
+    GEMM) is expected to beat the fused kernel for C[m, n] = A W^T, for a
+    caller who chooses between mixfp4_gemm and mixfp4_gemm_ws or holds
+    decoded operands; mixfp4_gemm(workspace="auto") has its own rule, with
+    the direct GEMM as a third route.  The
     decode costs (m + n) k elements of HBM traffic, the faster GEMM saves a
     share of 2 m n k flops, so it pays off from m n / (m + n) on.  Measured
     on MI355X (decode of W included): 16384x8192x8192 1626 against 1990 us,

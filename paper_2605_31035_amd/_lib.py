@@ -14,8 +14,8 @@ import torch  # noqa: F401  (loads the HIP runtime the library binds to)
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmixfp4.so")
 
 SYMBOLS = ("mixfp4_quantize_ws", "mixfp4_quantize_decode_ws",
-           "mixfp4_quantize_scratch_bytes", "mixfp4_quantize", "mixfp4_quantize_ex", "mixfp4_quantize_2d", "mixfp4_hadamard",
-           "mixfp4_dequantize",
+           "mixfp4_quantize_scratch_bytes", "mixfp4_quantize", "mixfp4_quantize_ex",
+           "mixfp4_quantize_2d", "mixfp4_hadamard", "mixfp4_dequantize",
            "mixfp4_gemm", "mixfp4_gemm_ws", "mixfp4_gemm_workspace_size",
            "mixfp4_gemm_auto", "mixfp4_gemm_auto_workspace_size",
            "mixfp4_decode_operand", "mixfp4_gemm_decoded", "mixfp4_gemm_noalloc",

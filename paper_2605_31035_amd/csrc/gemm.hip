@@ -671,13 +671,14 @@ __global__ __launch_bounds__(64 * kW * (kB > 0 ? 2 : 1)) void decode_step_kernel
 }
 
 // The same step for an A of at most kLocalPerThread blocks per thread of a
-// workgroup (a token, or a few of a narrow layer): every workgroup forms s32 and quantizes all of A itself,
-// into LDS, while its first W loads are in flight; nothing is handed over
-// between workgroups, and the first one also writes A's outputs.  A workgroup
-// then spends up to four blocks of quantizer arithmetic per thread (about a
-// microsecond each) instead of waiting ~9 us for the producers' count.  `sync` stays untouched.  Rows of A are padded by a 16-byte piece
-// and a scale word in LDS, so that the 16 rows of an A load start on
-// different banks.  1 x 11008 x 4096: 18.6 -> 10.5 us (8.9 the GEMM alone),
+// workgroup (a token, or a few of a narrow layer): every workgroup forms s32
+// and quantizes all of A itself, into LDS, while its first W loads are in
+// flight; nothing is handed over between workgroups, and the first one also
+// writes A's outputs.  A workgroup then spends up to four blocks of quantizer
+// arithmetic per thread (about a microsecond each) instead of waiting ~9 us
+// for the producers' count.  `sync` stays untouched.  Rows of A are padded by
+// a 16-byte piece and a scale word in LDS, so that the 16 rows of an A load
+// start on different banks.  1 x 11008 x 4096: 18.6 -> 10.5 us (8.9 the GEMM alone),
 // 4 x 11008 x 4096: 18.4 -> 13.0; eight blocks per thread would be even.
 constexpr int kLocalPerThread = 4;
 

@@ -480,11 +480,16 @@ __global__ __launch_bounds__(kT) void quantize_small_kernel(
 // partials[blockIdx.x] or, without partials, into *out by atomic max.
 // kStore: the rotated tensor itself goes to y [rows, k] as well, for the
 // quantize kernel to read instead of rotating X a second time: bound by the
-// fp64 butterflies and conversions, so from b = 128 on the store is cheaper than
-// repeating them.  Whole call with the scale computed, b = 128, rotated twice
-// against stored: 1537 x 4096 20.7 -> 19.7 us, 4096 x 4096 42.3 -> 34.3, 8192 x
-// 8192 143 -> 106, 16384 x 16384 542 -> 388.  b = 16 exchanges nothing between
-// lanes and loses: 14.4 -> 16.8, 26.7 -> 26.7, 83.8 -> 86, 320 -> 347.
+// fp64 butterflies and conversions, so the store is cheaper than repeating
+// them where there are enough of them.  Whole call with the scale computed,
+// rotated twice -> stored, us at 1537 x 4096, 4096 x 4096 and 8192 x 8192:
+//   b = 16   15.0 -> 16.7  27.1 -> 26.8  86.7 -> 86.5 (8192 x 4096: 45.7 -> 48.8)
+//   b = 32   17.5 -> 18.5  33.3 -> 30.2   107 -> 91
+//   b = 64   18.6 -> 18.6  36.6 -> 30.6   122 -> 94
+//   b = 128  21.2 -> 20.2  42.5 -> 34.6   145 -> 109
+//   b = 256  23.6 -> 21.1  49.4 -> 36.9   174 -> 118
+// It is taken from b = 128 on, where it wins at every size; b = 32 and 64, which
+// gain from about 16 M elements on, are rotated twice so far.
 template <bool kContig, bool kStore>
 __global__ __launch_bounds__(kThreads) void amax_rotated_kernel(
     const uint16_t* __restrict__ x, int64_t nbk, int64_t ldx, int64_t nblocks, HadamardParams hp,
@@ -720,12 +725,18 @@ hipError_t launch_mode(const uint16_t* x, int64_t rows, int64_t k, int64_t ldx, 
   if (ldx == k && !kHad) {
     // Contiguous X (stream_loop): one window of 64 blocks per wave, four
     // per workgroup; a tensor with more windows is walked by a persistent
-    // grid of at most 4 workgroups per CU.  Against 3 per CU, with the scale
-    // computed: 1537 x 4096 14.4 -> 13.5 us, 4096 x 4096 22.8 -> 21.1, 8192 x
-    // 8192 63 -> 60; s32 given, 2^28 elements 145 -> 141, with stochastic
-    // rounding 242 -> 232 (6 per CU: 17 us on 1537 x 4096).  The single-format
-    // encodings do little arithmetic per byte and stream better with 3 (E2M1
-    // on 2^28 elements 110 us against 115).
+    // grid of at most 4 workgroups per CU.  3 -> 4 per CU, s32 given, us at
+    // 1537 x 4096, 4096 x 4096, 8192 x 8192 and 8192 x 16384:
+    //   selection            8.6 -> 7.8  14.0 -> 12.2  39.1 -> 37.9  71.5 -> 68.2
+    //   4/6                  8.6 -> 7.9  14.4 -> 12.8  40.5 -> 38.9  75.5 -> 75.6
+    //   selection, SR       12.6 -> 11.4 21.9 -> 19.4  67.1 -> 62.4  124 -> 119
+    //   4/6, SR             12.7 -> 11.5 22.7 -> 20.3  68.5 -> 64.8  127 -> 122
+    //   one format, SR       9.1 -> 8.2  16.3 -> 14.5  48.8 -> 45.9  90.0 -> 86.3
+    // (the same order with the scale computed; no difference on 2^28 elements
+    // with the scale given; 6 per CU: 17 us on 1537 x 4096, scale computed,
+    // against 13.5).  The single-format encodings to nearest do little
+    // arithmetic per byte and stream better with 3 (E2M1 on 2^28 elements 110
+    // us against 115).
     constexpr int kStreamPerCU = !kSR && (kMode == kForceE2M1 || kMode == kForceE1M2) ? 3 : 4;
     const int64_t wanted = (nblocks + kThreads - 1) / kThreads;
     const int64_t capped =
