@@ -478,7 +478,7 @@ const char *mixfp4_last_launch_error(void);
 /* ABI version of this header (major * 100 + minor). */
 int mixfp4_abi_version(void);
 
-#define MIXFP4_ABI_VERSION 109
+#define MIXFP4_ABI_VERSION 110
 
 #ifdef __cplusplus
 }
