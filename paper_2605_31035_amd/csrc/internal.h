@@ -106,8 +106,8 @@ struct KeptRange {
     return in(from, to) || in(from2, to2);
   }
 };
-constexpr KeptRange kKeptNever{}, kKeptTransposed{32, 120}, kKept2d{32, 100, 148, 168},
-    kKeptDecode{32, 72}, kKeptVariant{32, 96};
+constexpr KeptRange kKeptNever{}, kKeptTransposed{32, 112}, kKept2d{32, 104, 138, 160},
+    kKeptDecode{32, 72}, kKeptVariant{32, 124};
 
 // Tensor scale s32 = max|X| / 2688 (1.0 for all-zero X) into *tensor_scale.
 // `scratch` (may be NULL) is device memory of `scratch_bytes` that the call

@@ -90,22 +90,23 @@ __global__ __launch_bounds__(kThreads) void amax_kernel(const uint16_t* __restri
 // end read zeros (buffer range check), which leave the maximum unchanged.
 // Where X is of a size in KeptRange it is loaded without the hint, so that the
 // pass behind finds it in the 256 MB infinity cache.  How long that pays
-// depends on what that pass writes beside it (us with -> without the hint, in
-// a loop over three tensors, 24 to 320 MB in steps of 4 to 32):
-//   2D, both layouts: 32 MB 28.1 -> 25.3, 64 MB 47.0 -> 40.2, 96 MB 66.6 ->
-//     57.5, 104 MB 71.2 -> 73.0, 128 MB 85.5 -> 92.1, 140 MB 93.2 -> 95.7,
-//     160 MB 106 -> 96, 168 MB 110 -> 110, 200 MB 131 -> 141
-//   decode fused: 32 MB 26.8 -> 26.0, 64 MB 45.0 -> 42.8, 72 MB 49.4 -> 48.6,
-//     80 MB 54.4 -> 55.3, 128 MB 82.4 -> 96.1
-//   transposed: 32 MB 23.9 -> 22.8, 120 MB 65.5 -> 62.3, 152 MB 82.3 -> 83.8
-//   variant: 32 MB 29.1 -> 28.7, 96 MB 71.9 -> 71.7, 128 MB 93.3 -> 94.7
-//   1D, never: 32 MB 21.1 -> 21.0, 64 MB 34.7 -> 34.1, 160 MB 74.7 -> 73.0,
-//     but the GEMM behind pays more for X in the cache (linear 4096 x 11008 x
-//     5008 1202 -> 1229 us, 5120 x 8192 x 4096 338 -> 343, 8192 x 4096 x 8208
-//     1343 -> 1375), and with stochastic rounding the call itself loses
-//     (117 MB 82.1 -> 82.9, backward 4096 x 14336 x 4096 1044 -> 1058)
-// Smaller ones stay there anyway, and the pass itself is faster with the hint
-// (1537 x 4096: 14.4 against 14.8 us).
+// depends on what that pass writes beside it.  Time with the hint over time
+// without it, a loop over three tensors, six widths from 4096 to 14336 (two
+// for the transposed call and the variants), sizes in MB:
+//   2D, both layouts: 32 1.10-1.24, 64 1.18-1.28, 100 1.03-1.22, 104 0.93-1.05,
+//     128 0.92-0.96, 136 0.93-1.00, 140 0.96-1.06, 156 1.02-1.13, 164
+//     0.95-1.10, 172 0.94-1.03
+//     (8192 wide: 64 MB 47.0 -> 40.2 us, 128 MB 85.5 -> 92.1, 156 MB 102 -> 96)
+//   decode fused: 32 1.02-1.04, 72 1.02-1.06, 80 0.96-1.02, 128 0.78-0.85
+//   transposed: 32 1.08-1.12, 112 1.03-1.05, 120 0.93-1.05, 136 0.83-0.89
+//   variant: 32 1.03, 120 1.00-1.03, 128 0.99-1.01, 164 0.97
+//   1D, never: 1.00-1.02 up to 144 MB, but the GEMM behind pays more for X in
+//     the cache (linear 4096 x 11008 x 5008 1202 -> 1229 us, 5120 x 8192 x 4096
+//     338 -> 343, 8192 x 4096 x 8208 1343 -> 1375), and with stochastic rounding
+//     the call itself loses (117 MB 82.1 -> 82.9 us, backward 4096 x 14336 x
+//     4096 1044 -> 1058)
+// Below, the pass itself is faster with the hint (1D 1537 x 4096: 14.4 against
+// 14.8 us).
 constexpr int kNonTemporal = 2;
 constexpr int kAmaxWindow = 256;      // vectors of 8 bf16 per wave per iteration
 

@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kind,mb", [(kind, mb) for kind, edges in (
-    ("2d", (31, 32, 100, 101, 147, 148, 168, 169)), ("decode", (31, 32, 72, 73)),
-    ("transpose", (31, 32, 120, 121)), ("variant", (31, 32, 96, 97)), ("1d", (32, 128)))
+    ("2d", (31, 32, 104, 105, 137, 138, 160, 161)), ("decode", (31, 32, 72, 73)),
+    ("transpose", (31, 32, 112, 113)), ("variant", (31, 32, 124, 125)), ("1d", (32, 128)))
     for mb in edges])
 def test_kept_ranges(kind, mb):
     import paper_2605_31035_amd as M
